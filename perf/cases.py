@@ -1,0 +1,417 @@
+"""The work that users of this library have it do, as timed cases.
+
+Kinds of case, each one pass through the public entry points:
+
+  linear    one training step of a linear layer: q2d_linear_fwd, then
+            q2d_linear_bwd (X and W quantized once, dY quantized once, the three
+            GEMMs); 2D blocks of 32 or 64, 1D activations, round to nearest or
+            stochastic rounding, float32 or bfloat16 tensors
+  module    one training step of Q2DLinear under autograd: float32 master
+            weight, bfloat16 activations [batch, seq, features]
+  infer     evaluation with a weight that is quantized once and kept: quantize
+            the new activations, forward GEMM
+  mxfp8     one training step of a query/key projection in MXFP8: three
+            quantizations and three GEMMs
+  moe       one training step of the expert matrices of a mixture-of-experts
+            layer: grouped quantizations, ragged-M forward and data gradient,
+            ragged-K weight gradient
+  chain     a linear layer inside an FP4 network: the forward output (round to
+            nearest) and the data gradient (stochastic) are delivered in FP4 by
+            the GEMM's epilogue
+  export    a float32 master weight quantized and written back as the bfloat16
+            values that the GEMMs see (checkpoint export, error reports)
+
+Sizes are those of the repository's configurations (Tiny, 1B, 7B, 30B MoE), of
+its tests, or generic.
+"""
+import math
+
+import torch
+
+import paper_2607_24953_amd as q2d
+from paper_2607_24953_amd.autograd import Q2DLinear
+
+DEV = "cuda:0"
+
+
+# ---------------------------------------------------------------- the cases
+
+def listed():
+    return [
+        # the Tiny configuration: a unit-test sized layer, where launches and host calls count
+        dict(name="tiny_f32", kind="linear", T=128, N=256, K=256, dtype="f32", mode="sr", dy="sr",
+             block=32, oned=False, outliers=False),
+        # nothing a multiple of anything: a classifier-like layer on a ragged batch, float32
+        dict(name="odd_f32", kind="linear", T=1999, N=1003, K=1111, dtype="f32", mode="rtn", dy="sr",
+             block=32, oned=False, outliers=False),
+        # the 1B-class up projection, stochastic rounding on every operand
+        dict(name="up_1b", kind="linear", T=8192, N=5632, K=2048, dtype="bf16", mode="sr", dy="sr",
+             block=32, oned=False, outliers=False),
+        # the 7B-class QKV projection with outlier channels: the largest
+        dict(name="qkv_7b", kind="linear", T=16384, N=12288, K=4096, dtype="bf16", mode="rtn", dy="sr",
+             block=32, oned=False, outliers=True),
+        # the paper's activation placement (1D blocks) on one 4096-token sequence, 7B output projection
+        dict(name="o_1d", kind="linear", T=4096, N=4096, K=4096, dtype="bf16", mode="rtn", dy="sr",
+             block=32, oned=True, outliers=True),
+        # a micro-batch of four ragged sequences through the autograd layer
+        dict(name="module_2k", kind="module", B=4, T=500, N=2048, K=2048, mode="rtn", dy="sr",
+             block=32, oned=False),
+        # evaluation, a few tokens against the kept 7B QKV weight (decode)
+        dict(name="decode_qkv", kind="infer", T=16, N=12288, K=4096, oned=False),
+        # evaluation, one ragged prompt against the kept 7B gate weight (prefill), 1D activations
+        dict(name="prefill_gate", kind="infer", T=777, N=11008, K=4096, oned=True),
+        # one query or key projection of the 7B-class block in MXFP8, two sequences
+        dict(name="qk_mxfp8", kind="mxfp8", T=8192, N=4096, K=4096),
+        # the 30B-class MoE gate/up matrices, Zipf routing of 16384 tokens
+        dict(name="moe_30b_gu", kind="moe", tokens=16384, experts=128, topk=8, N=1536, K=2048),
+        # a small MoE on a short, ragged batch
+        dict(name="moe_small", kind="moe", tokens=1500, experts=32, topk=4, N=1024, K=1024),
+        # FP4 in, FP4 out: 7B output projection on one sequence
+        dict(name="chain_o", kind="chain", T=4096, N=4096, K=4096),
+    ]
+
+
+def _log(rng, lo, hi, step=1):
+    """Log-uniform in [lo, hi], rounded to a multiple of step."""
+    v = math.exp(rng.uniform(math.log(lo), math.log(hi)))
+    return max(step, min(hi, int(round(v / step)) * step))
+
+
+# 2 T N K of one GEMM of the largest listed case
+_MOST = 2.0 * 16384 * 12288 * 4096
+
+
+def _features(rng):
+    """A feature count: mostly whole multiples of 64, some of 8, some odd."""
+    return _log(rng, 256, 12288, rng.choice([64, 64, 64, 128, 8, 1]))
+
+
+def draw(rng):
+    """One more case of the ranges above."""
+    kind = rng.choice(["linear", "linear", "linear", "module", "infer", "infer", "mxfp8", "moe", "chain", "export"])
+    if kind == "moe":
+        experts = rng.choice([8, 16, 32, 60, 64, 128])
+        return dict(kind=kind, tokens=_log(rng, 256, 16384), experts=experts, topk=rng.choice([2, 4, 8]),
+                    N=_log(rng, 256, 1536, 32), K=_log(rng, 256, 2048, 128))
+    while True:
+        T, N, K = _log(rng, 64, 16384), _features(rng), _features(rng)
+        if kind == "infer":
+            T = _log(rng, 1, 4096)
+        if kind == "chain":
+            N, K = (N + 7) // 8 * 8, (K + 7) // 8 * 8
+        # float32 tensors and MXFP8 products cost about twice as much
+        dtype = rng.choice(["bf16", "bf16", "bf16", "f32"])
+        if dtype == "f32":
+            T = min(T, 4096)
+        most = 0.4 if kind == "mxfp8" or (kind == "linear" and dtype == "f32") else 0.9
+        if 2.0 * T * N * K <= most * _MOST and N * K <= 12288 * 4096:
+            break
+    if kind == "linear":
+        oned = rng.random() < 0.25
+        return dict(kind=kind, T=T, N=N, K=K, dtype=dtype, mode=rng.choice(["rtn", "rtn", "sr"]), dy="sr",
+                    block=32 if oned or rng.random() < 0.75 else 64, oned=oned, outliers=rng.random() < 0.5)
+    if kind == "module":
+        B = rng.choice([1, 2, 4, 8])
+        return dict(kind=kind, B=B, T=max(1, min(T, 8192) // B), N=N, K=K, mode="rtn", dy="sr",
+                    block=rng.choice([32, 32, 64]), oned=rng.random() < 0.25)
+    if kind == "infer":
+        return dict(kind=kind, T=T, N=N, K=K, oned=rng.random() < 0.3)
+    if kind == "export":
+        return dict(kind=kind, N=N, K=K, block=rng.choice([32, 64]), copy=rng.choice([0, 1]))
+    return dict(kind=kind, T=T, N=N, K=K)
+
+
+# ---------------------------------------------------------------- inputs
+
+def _gen(seed, k):
+    g = torch.Generator(device=DEV)
+    g.manual_seed(seed * 1009 + k)
+    return g
+
+
+def _normal(shape, std, seed, k, dtype):
+    return torch.randn(shape, generator=_gen(seed, k), device=DEV).mul_(std).to(dtype)
+
+
+def _outliers(x, seed, k):
+    """1 % of the channels replaced by 20 x Student-t(3) samples."""
+    rows, cols = x.shape
+    n = max(1, round(0.01 * cols))
+    g = _gen(seed, k)
+    idx = torch.randperm(cols, generator=g, device=DEV)[:n]
+    z = torch.randn((4, rows, n), generator=g, device=DEV)
+    x[:, idx] = (20.0 * z[0] / torch.sqrt((z[1] * z[1] + z[2] * z[2] + z[3] * z[3]) / 3)).to(x.dtype)
+    return x
+
+
+def _routing(case, seed):
+    """Rows per expert: top-k of Zipf(1.1) weights plus Gumbel noise, a fresh rank order per seed."""
+    g = _gen(seed, 9)
+    rank = torch.randperm(case["experts"], generator=g, device=DEV).double() + 1
+    u = torch.rand((case["tokens"], case["experts"]), generator=g, device=DEV, dtype=torch.float64)
+    pick = (-1.1 * rank.log() - (-u.log()).log()).topk(case["topk"], dim=1).indices
+    counts = torch.bincount(pick.flatten(), minlength=case["experts"])
+    return torch.cat([counts.new_zeros(1), counts.cumsum(0)])
+
+
+def _tensors(case, seed):
+    """X ~ N(0, 1), W ~ N(0, 0.02), dY ~ N(0, 1e-3), as in the training configurations."""
+    kind = case["kind"]
+    dt = torch.float32 if case.get("dtype") == "f32" else torch.bfloat16
+    N, K = case["N"], case["K"]
+    if kind == "moe":
+        T, E = case["tokens"] * case["topk"], case["experts"]
+        return dict(X=_normal((T, K), 1.0, seed, 1, dt), W=_normal((E * N, K), 0.02, seed, 2, dt),
+                    dY=_normal((T, N), 1e-3, seed, 3, dt), off=_routing(case, seed))
+    if kind == "export":
+        return dict(W=_normal((N, K), 0.02, seed, 2, torch.float32))
+    T = case["T"] * case.get("B", 1)
+    t = dict(X=_normal((T, K), 1.0, seed, 1, dt),
+             W=_normal((N, K), 0.02, seed, 2, torch.float32 if kind == "module" else dt),
+             dY=_normal((T, N), 1e-3, seed, 3, dt))
+    if case.get("outliers") or kind == "mxfp8":
+        _outliers(t["X"], seed, 4)
+    return t
+
+
+def prepare(case, seed):
+    s = dict(_tensors(case, seed), case=case, seed=seed)
+    kind = case["kind"]
+    if kind == "infer":
+        s["qW"] = q2d.q2d_quantize(s.pop("W"))
+        del s["dY"]
+    elif kind == "module":
+        layer = Q2DLinear(case["K"], case["N"], mode_x=case["mode"], mode_w=case["mode"], mode_dy=case["dy"],
+                          activations="1d" if case["oned"] else "2d", block=case["block"], seed=seed, device=DEV)
+        layer.weight.data.copy_(s.pop("W"))
+        s["layer"] = layer
+        s["X"] = s["X"].view(case["B"], case["T"], case["K"]).requires_grad_()
+        s["dY"] = s["dY"].view(case["B"], case["T"], case["N"])
+    elif kind == "chain":
+        # operands arrive in FP4 from the neighbouring layers
+        s["qX"] = q2d.q2d_quantize(s.pop("X"))
+        s["qdY"] = q2d.q2d_quantize(s.pop("dY"), "sr", seed, 2)
+    return s
+
+
+# ---------------------------------------------------------------- one pass
+
+def run(s):
+    c, seed = s["case"], s["seed"]
+    kind = c["kind"]
+    if kind == "linear":
+        fmt = q2d.FP4_1D if c["oned"] else q2d.FP4_2D
+        y_dt = torch.float32 if c["dtype"] == "f32" else torch.bfloat16
+        Y, qX, qW = q2d.q2d_linear_fwd(s["X"], s["W"], c["mode"], c["mode"], seed, 0, 1, y_dtype=y_dt, fmt_x=fmt,
+                                       block=c["block"])
+        dX, dW, _ = q2d.q2d_linear_bwd(s["dY"], qX, qW, c["dy"], seed, 2, dx_dtype=y_dt, block=c["block"])
+        return dict(Y=Y, dX=dX, dW=dW)
+    if kind == "module":
+        x, layer = s["X"], s["layer"]
+        x.grad = layer.weight.grad = None
+        Y = layer(x)
+        Y.backward(s["dY"])
+        return dict(Y=Y.detach(), dX=x.grad, dW=layer.weight.grad)
+    if kind == "infer":
+        qX = q2d.q2d_quantize_1d(s["X"]) if c["oned"] else q2d.q2d_quantize(s["X"])
+        return q2d.q2d_gemm(qX, 0, s["qW"], 0, out_dtype=torch.bfloat16)
+    if kind == "mxfp8":
+        qX, qW = q2d.mxfp8_quantize(s["X"]), q2d.mxfp8_quantize(s["W"])
+        Y = q2d.q2d_gemm(qX, 0, qW, 0, out_dtype=torch.bfloat16)
+        qdY = q2d.mxfp8_quantize(s["dY"])
+        return dict(Y=Y, dX=q2d.q2d_gemm(qdY, 0, qW, 1, out_dtype=torch.bfloat16), dW=q2d.q2d_gemm(qdY, 1, qX, 1))
+    if kind == "moe":
+        off = s["off"]
+        qX, qW = q2d.q2d_grouped_quantize(s["X"], off), q2d.q2d_quantize(s["W"])
+        Y = q2d.q2d_grouped_gemm(qX, 0, qW, 0, off, out_dtype=torch.bfloat16)
+        qdY = q2d.q2d_grouped_quantize(s["dY"], off, "sr", seed, 2)
+        dX = q2d.q2d_grouped_gemm(qdY, 0, qW, 1, off, out_dtype=torch.bfloat16)
+        return dict(Y=Y, dX=dX, dW=q2d.q2d_grouped_gemm(qdY, 1, qX, 1, off))
+    if kind == "chain":
+        qW = q2d.q2d_quantize(s["W"])
+        qY = q2d.q2d_gemm_quantized(s["qX"], 0, qW, 0)
+        qdX = q2d.q2d_gemm_quantized(s["qdY"], 0, qW, 1, "sr", seed=seed, offset=5)
+        dW = q2d.q2d_gemm(s["qdY"], 1, s["qX"], 1)
+        return dict(dW=dW, Y=[qY.codes, qY.codes_t, qY.scales, qY.scales_t],
+                    dX=[qdX.codes, qdX.codes_t, qdX.scales, qdX.scales_t])
+    qW = q2d.q2d_quantize(s["W"], block=c["block"])
+    return dict(W=q2d.q2d_dequantize(qW, c["copy"], torch.bfloat16),
+                q=[qW.codes, qW.codes_t, qW.scales, qW.scales_t])
+
+
+# ---------------------------------------------------------------- floors and tolerances
+
+def work(case):
+    """Inputs read once, outputs written once (the quantized operands stay inside a
+    pass and are not counted, except where they are what is read or returned)."""
+    kind, N, K = case["kind"], case["N"], case["K"]
+    fp4 = 0.5 + 1.0 / 1024                  # bytes per element of one stored FP4 copy with its scales
+    if kind == "export":
+        return {"bytes": N * K * (4 + 2 * fp4 + 2), "flops": 0}
+    if kind == "moe":
+        T, E = case["tokens"] * case["topk"], case["experts"]
+        return {"bytes": 2 * T * (K + N) + 2 * E * N * K + 2 * T * (N + K) + 4 * E * N * K, "flops": 6.0 * T * N * K}
+    T = case["T"] * case.get("B", 1)
+    if kind == "infer":
+        return {"bytes": 2 * T * K + fp4 * N * K + 2 * T * N, "flops": 2.0 * T * N * K}
+    if kind == "chain":
+        return {"bytes": 2 * fp4 * T * (K + N) + 2 * N * K + 2 * fp4 * T * (N + K) + 4 * N * K, "flops": 6.0 * T * N * K}
+    x = 4 if case.get("dtype") == "f32" else 2
+    w = 4 if kind == "module" else x
+    return {"bytes": x * T * (K + N) + w * N * K + x * T * (N + K) + 4 * N * K, "flops": 6.0 * T * N * K}
+
+
+def tolerance(case):
+    """Measured against exact(): a bfloat16 result differs by its one rounding, 1.7e-3.
+    A float32 result of FP4 products is exact at these sizes (sums of multiples of
+    a quarter of two block scales, below 2^24 of them) and may lose a few float32
+    roundings where block scales lie far apart.  The MXFP8 products are truncated
+    inside the matrix instruction (3e-5), below the bfloat16 rounding of Y and dX.
+    FP4 outputs of `chain` are whole values: a sum that falls on a rounding
+    boundary may go either way."""
+    kind = case["kind"]
+    if kind == "export":
+        return "exact"
+    if kind == "chain":
+        return {"rel": 1e-6, "max": 1e-4, "differ": 1e-4}
+    if case.get("dtype") == "f32":
+        return {"rel": 1e-6, "max": 1e-4}
+    return {"rel": 7e-3, "max": 0.016}
+
+
+# ---------------------------------------------------------------- 64-bit results in plain torch
+
+def _exponent(amax, top):
+    """Smallest e with top * 2^e >= amax, for top = f * 2^p (clamped below at -127)."""
+    f, p = math.frexp(top)
+    m, q = torch.frexp(amax)
+    e = q - p + (m > f).to(q.dtype)
+    return torch.where(amax > 0, e, torch.full_like(e, -127)).clamp_min(-127)
+
+
+def _pow2(e):
+    """2^e as float64 from its bits (torch.ldexp goes through a float32 pow, which is not exact on the GPU)."""
+    return ((e.to(torch.int64) + 1023) << 52).view(torch.float64)
+
+
+def _blocks_max(x, br, bc):
+    """Maximum magnitude of every br x bc block, expanded to the elements."""
+    R, C = x.shape
+    a = torch.nn.functional.pad(x.abs(), (0, -C % bc, 0, -R % br))
+    m = a.view(a.shape[0] // br, br, a.shape[1] // bc, bc).amax(dim=(1, 3))
+    return m.repeat_interleave(br, 0).repeat_interleave(bc, 1)[:R, :C]
+
+
+_GRID = (0.0, 0.5, 1.0, 1.5, 2.0, 3.0, 4.0, 6.0)
+
+
+def _mul32(a, b):
+    """High and low words of the product of 32-bit values (int64 tensors; b an int)."""
+    al, ah, bl, bh = a & 0xFFFF, a >> 16, b & 0xFFFF, b >> 16
+    ll, lh, hl = al * bl, al * bh, ah * bl
+    mid = (ll >> 16) + (lh & 0xFFFF) + (hl & 0xFFFF)
+    return ah * bh + (lh >> 16) + (hl >> 16) + (mid >> 16), ((mid & 0xFFFF) << 16) | (ll & 0xFFFF)
+
+
+def _draws(first, n, seed, offset):
+    """The 16-bit draws of storage indices first .. first + n - 1 (Philox4x32-10, counter
+    (index >> 3, offset), key seed; half index & 1 of word (index & 7) >> 1)."""
+    g0 = first >> 3
+    g = torch.arange(g0, ((first + n - 1) >> 3) + 1, device=DEV, dtype=torch.int64)
+    c0, c1 = g & 0xFFFFFFFF, g >> 32
+    c2, c3 = torch.full_like(g, offset & 0xFFFFFFFF), torch.full_like(g, offset >> 32)
+    k0, k1 = seed & 0xFFFFFFFF, seed >> 32
+    for r in range(10):
+        h0, l0 = _mul32(c0, 0xD2511F53)
+        h1, l1 = _mul32(c2, 0xCD9E8D57)
+        c0, c1, c2, c3 = h1 ^ c1 ^ k0, l1, h0 ^ c3 ^ k1, l0
+        k0, k1 = (k0 + 0x9E3779B9) & 0xFFFFFFFF, (k1 + 0xBB67AE85) & 0xFFFFFFFF
+    w = torch.stack([c0 & 0xFFFF, c0 >> 16, c1 & 0xFFFF, c1 >> 16, c2 & 0xFFFF, c2 >> 16, c3 & 0xFFFF, c3 >> 16], 1)
+    return w.view(-1)[first - 8 * g0:first - 8 * g0 + n]
+
+
+def _fp4(x, amax, mode, seed, offset, first=0):
+    """E2M1 values of x (a row-major matrix whose first element has storage index `first`)
+    with the block maxima amax; mode "rtn" or "sr"."""
+    scale = _pow2(_exponent(amax, 6.0))
+    v = x.abs() / scale
+    grid = torch.tensor(_GRID, device=DEV, dtype=torch.float64)
+    if mode == "rtn":
+        # ties go to the even grid index
+        idx = sum((v > b).to(torch.int64) for b in (0.25, 1.25, 2.5, 5.0))
+        idx += sum((v >= b).to(torch.int64) for b in (0.75, 1.75, 3.5))
+    else:
+        idx = sum((v >= b).to(torch.int64) for b in _GRID[1:])
+        step = grid[(idx + 1).clamp_max(7)] - grid[idx]
+        frac = torch.where(step > 0, (65536 * ((v - grid[idx]) / step.clamp_min(0.5))).floor(), torch.zeros_like(v))
+        r = _draws(first, x.numel(), seed, offset).view(x.shape)
+        idx += (frac + r >= 65536).to(torch.int64)
+    return torch.copysign(grid[idx], x) * scale
+
+
+def _q2(x, mode="rtn", seed=0, offset=0, block=32, first=0):
+    x = x.double()
+    return _fp4(x, _blocks_max(x, block, block), mode, seed, offset, first)
+
+
+def _q1(x, mode, seed, offset):
+    """The forward (1 x 32) and the backward (32 x 1) copy of a 1D-block activation."""
+    x = x.double()
+    return _fp4(x, _blocks_max(x, 1, 32), mode, seed, offset), _fp4(x, _blocks_max(x, 32, 1), mode, seed, offset)
+
+
+def _q8(x):
+    """The rowwise (1 x 32) and the colwise (32 x 1) MXFP8 copy: E4M3, round to nearest even."""
+    x = x.double()
+
+    def copy(amax):
+        scale = _pow2(_exponent(amax, 448.0))
+        v = x / scale
+        e = (torch.frexp(v)[1] - 1).clamp_min(-6)
+        q = _pow2(e - 3)
+        return torch.round(v / q) * q * scale
+
+    return copy(_blocks_max(x, 1, 32)), copy(_blocks_max(x, 32, 1))
+
+
+def exact(case, seed):
+    t = _tensors(case, seed)
+    kind = case["kind"]
+    if kind == "export":
+        return dict(W=_q2(t["W"], block=case["block"]), q=[None] * 4)
+    if kind == "infer":
+        X = _q1(t["X"], "rtn", 0, 0)[0] if case["oned"] else _q2(t["X"])
+        return X @ _q2(t["W"]).t()
+    if kind == "mxfp8":
+        (Xr, Xc), (Wr, Wc), (Gr, Gc) = _q8(t["X"]), _q8(t["W"]), _q8(t["dY"])
+        return dict(Y=Xr @ Wr.t(), dX=Gr @ Wc, dW=Gc.t() @ Xc)
+    if kind == "chain":
+        dW = _q2(t["dY"], "sr", seed, 2).t() @ _q2(t["X"])
+        return dict(dW=dW, Y=[None] * 4, dX=[None] * 4)
+    if kind == "moe":
+        N, K = case["N"], case["K"]
+        W, off = _q2(t["W"]), t["off"].tolist()
+        T = t["X"].shape[0]
+        Y = torch.zeros((T, N), device=DEV, dtype=torch.float64)
+        dX = torch.zeros((T, K), device=DEV, dtype=torch.float64)
+        dW = torch.zeros((case["experts"] * N, K), device=DEV, dtype=torch.float64)
+        for e, (a, b) in enumerate(zip(off, off[1:])):
+            if a == b:
+                continue
+            X = _q2(t["X"][a:b])
+            dY = _q2(t["dY"][a:b], "sr", seed, 2, first=a * N)
+            We = W[e * N:(e + 1) * N]
+            Y[a:b] = X @ We.t()
+            dX[a:b] = dY @ We
+            dW[e * N:(e + 1) * N] = dY.t() @ X
+        return dict(Y=Y, dX=dX, dW=dW)
+    mode, block = case["mode"], case["block"]
+    w = t["W"].to(t["X"].dtype)             # the module casts its master weight to the activations' type
+    W = _q2(w, mode, seed, 1, block)
+    Xf, Xb = _q1(t["X"], mode, seed, 0) if case["oned"] else (_q2(t["X"], mode, seed, 0, block),) * 2
+    dY = _q2(t["dY"], case["dy"], seed, 2, block)
+    r = dict(Y=Xf @ W.t(), dX=dY @ W, dW=dY.t() @ Xb)
+    if kind == "module":
+        lead = (case["B"], case["T"])
+        r["Y"], r["dX"] = r["Y"].view(*lead, -1), r["dX"].view(*lead, -1)
+    return r
