@@ -92,7 +92,7 @@ def draw(rng):
     if kind == "moe":
         experts = rng.choice([8, 16, 32, 60, 64, 128])
         return dict(kind=kind, tokens=_log(rng, 256, 16384), experts=experts, topk=rng.choice([2, 4, 8]),
-                    N=_log(rng, 256, 1536, 32), K=_log(rng, 256, 2048, 128))
+                    N=_log(rng, 256, 1536, 128), K=_log(rng, 256, 2048, 128))
     while True:
         T, N, K = _log(rng, 64, 16384), _features(rng), _features(rng)
         if kind == "infer":
