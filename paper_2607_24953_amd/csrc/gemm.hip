@@ -11,20 +11,11 @@
 // what lets one quantization serve Y = X W^T, dX = dY W and dW = dY^T X.  For
 // MXFP8 each row has its own scale per K-group.
 //
-// Two kernels.  Problems with at least 128 output tiles of 256 x 256 run on the
-// persistent large-tile kernels further down (gemm_fp4_persistent_kernel, also
-// the grouped and quantized-output forms, and gemm_fp8_256_kernel).  Smaller
-// problems use gemm_kernel: 256 threads, 128 x 128 output tile, 2 x 2 waves of
-// 64 x 64 (2 x 2 MFMA tiles each), K-tile of 128 elements staged in LDS with
-// double buffering.  LDS rows are XOR-swizzled in 16-byte chunks (Fmt::swz) so
-// that the MFMA operand reads hit distinct banks.  Workgroups are remapped so
-// that each XCD (one L2) walks a contiguous band of output tiles, grouped by 8
-// row tiles for operand reuse.
+// The kernels of this file take 256 x 256 output tiles: gemm_fp4_persistent_kernel
+// (dense, grouped and quantized-output FP4) and gemm_fp8_256_kernel.  Problems
+// with too few such tiles run on the small-tile kernels of gemm_small.hip.
 #include <atomic>
-#include <type_traits>
-#include <utility>
-#include "device_common.hpp"
-#include "kernels.hpp"
+#include "gemm_common.hpp"
 
 namespace q2d {
 
@@ -44,225 +35,10 @@ int cu_count()
 
 namespace {
 
-constexpr int BM = 128, BN = 128, BK = 128;
-constexpr int kThreads = 256;
 // row tiles per group of the XCD-aware raster: an XCD's 32 concurrent tiles
 // form a 4 x 8 block (measured against 2, 3, 8 and 16: 4 is fastest over the
 // 7B shapes, most of all on the short-K GEMMs with large outputs)
 constexpr int kGroupM = 4;
-constexpr int kXcds = 8;
-
-template <int FMT>
-struct Fmt;
-
-// Operand placement measured on gfx950 for v_mfma_scale_f32_32x32x64_f8f6f4:
-// with E2M1 operands (4 VGPRs) lane l holds 32 consecutive K values of K-group
-// l / 32; with E4M3 operands (8 VGPRs) the first 16 bytes of every lane belong
-// to K-group 0 and the last 16 bytes to K-group 1, the two lane halves splitting
-// each group.  In both cases lane half h supplies the scale of K-group h.
-// chunk(ks, half, h) is the 16-byte chunk of the K-tile row that feeds VGPRs
-// 4h..4h+3 of a lane in half `half` for K-substep ks (64 K values).
-template <>
-struct Fmt<kFmtFp4Block2D> {
-    static constexpr int kRowBytes = BK / 2;      // 64 bytes of codes per row per K-tile
-    static constexpr int kLaneBytes = 16;         // 32 E2M1 codes per lane per MFMA
-    static constexpr int kCbsz = 4;               // E2M1
-    static constexpr int kScaleRowShift = 5;      // one scale per 32-row block
-    // 16-byte chunk swizzle of 64-byte LDS rows, conflict-free for the fragment
-    // reads: rows r and r + 2 (read together with both lane halves) differ in
-    // chunk bit 1, and rows r, r + 4, r + 8, r + 12 get four distinct chunks
-    // (zero LdsBankConflict measured with rocprofv3)
-    static __device__ __forceinline__ int swz(int r) { return ((r & 2) ^ (r >> 2)) & 3; }
-    static __device__ __forceinline__ int chunk(int ks, int half, int) { return 2 * ks + half; }
-};
-
-template <>
-struct Fmt<kFmtMxfp8> {
-    static constexpr int kRowBytes = BK;          // 128 bytes per row per K-tile
-    static constexpr int kLaneBytes = 32;         // 32 E4M3 codes per lane per MFMA
-    static constexpr int kCbsz = 0;               // E4M3
-    static constexpr int kScaleRowShift = 0;      // one scale per row and K-group
-    // 16-byte chunk swizzle of 128-byte LDS rows: the four rows read together with
-    // both lane halves map to distinct chunk pairs, and eight consecutive rows to
-    // distinct chunks (zero LdsBankConflict measured with rocprofv3)
-    static __device__ __forceinline__ int swz(int r)
-    {
-        return ((r & 2) << 1) | (((r ^ (r >> 3)) & 1) << 1) | ((r >> 2) & 1);
-    }
-    static __device__ __forceinline__ int chunk(int ks, int half, int h) { return 4 * ks + 2 * h + half; }
-};
-
-__device__ __forceinline__ void tile_coords_of(int64_t bid, int64_t tiles_m, int64_t tiles_n, int64_t &tm, int64_t &tn)
-{
-    // Hardware dispatch sends consecutive workgroups to consecutive XCDs; give
-    // every XCD a contiguous range of the tile order instead.
-    const int64_t nb = tiles_m * tiles_n;
-    const int64_t xcd = bid % kXcds, local = bid / kXcds;
-    const int64_t per = nb / kXcds, rem = nb % kXcds;
-    const int64_t t = xcd * per + (xcd < rem ? xcd : rem) + local;
-    // grouped order: kGroupM row tiles sweep all column tiles together
-    const int64_t span = (int64_t)kGroupM * tiles_n;
-    const int64_t grp = t / span;
-    const int64_t first = grp * kGroupM;
-    const int64_t gsz = (tiles_m - first) < kGroupM ? (tiles_m - first) : kGroupM;
-    const int64_t in = t - grp * span;
-    tm = first + in % gsz;
-    tn = in / gsz;
-}
-
-__device__ __forceinline__ void tile_coords(int64_t tiles_m, int64_t tiles_n, int64_t &tm, int64_t &tn)
-{
-    tile_coords_of(blockIdx.x, tiles_m, tiles_n, tm, tn);
-}
-
-template <int FMT, bool BF16OUT>
-__global__ __launch_bounds__(kThreads) void gemm_kernel(const GemmArgs g, int64_t tiles_m, int64_t tiles_n)
-{
-    using F = Fmt<FMT>;
-    constexpr int RB = F::kRowBytes;
-    constexpr int NCH = RB / 16;                    // 16-byte chunks per row
-    constexpr int LOADS = (BM * NCH) / kThreads;    // chunks per thread per operand
-    __shared__ __attribute__((aligned(16))) uint8_t As[2][BM * RB];
-    __shared__ __attribute__((aligned(16))) uint8_t Bs[2][BN * RB];
-
-    int64_t tm, tn;
-    tile_coords(tiles_m, tiles_n, tm, tn);
-    const int64_t m0 = tm * BM, n0 = tn * BN;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wm = wave >> 1, wn = wave & 1;
-    const int64_t nk = g.K / BK;
-
-    // ---- global -> LDS staging addresses (rows clamped into the operand)
-    const uint8_t *ga[LOADS];
-    const uint8_t *gb[LOADS];
-    int lds_off[LOADS];
-#pragma unroll
-    for (int s = 0; s < LOADS; ++s) {
-        const int q = tid + s * kThreads;
-        const int r = q / NCH, c = q % NCH;
-        int64_t ra = m0 + r; ra = ra < g.M ? ra : g.M - 1;
-        int64_t rb = n0 + r; rb = rb < g.N ? rb : g.N - 1;
-        ga[s] = g.a + ra * g.lda + c * 16;
-        gb[s] = g.b + rb * g.ldb + c * 16;
-        lds_off[s] = r * RB + ((c ^ F::swz(r)) * 16);
-    }
-
-    // ---- per-lane scale rows (clamped)
-    const uint8_t *sa_row[2];
-    const uint8_t *sb_row[2];
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-        int64_t ra = m0 + wm * 64 + i * 32 + (lane & 31); ra = ra < g.M ? ra : g.M - 1;
-        int64_t rb = n0 + wn * 64 + i * 32 + (lane & 31); rb = rb < g.N ? rb : g.N - 1;
-        // 1x32 FP4 scales are K-tile-major words (row offset 4 r, K-tile stride ld)
-        sa_row[i] = g.a1d ? g.sa + ra * 4 : g.sa + (ra >> F::kScaleRowShift) * g.ldsa;
-        sb_row[i] = g.b1d ? g.sb + rb * 4 : g.sb + (rb >> F::kScaleRowShift) * g.ldsb;
-    }
-
-    v16f acc[2][2];
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
-
-    uint4 ra_reg[LOADS], rb_reg[LOADS];
-#pragma unroll
-    for (int s = 0; s < LOADS; ++s) {
-        ra_reg[s] = *reinterpret_cast<const uint4 *>(ga[s]);
-        rb_reg[s] = *reinterpret_cast<const uint4 *>(gb[s]);
-    }
-#pragma unroll
-    for (int s = 0; s < LOADS; ++s) {
-        *reinterpret_cast<uint4 *>(&As[0][lds_off[s]]) = ra_reg[s];
-        *reinterpret_cast<uint4 *>(&Bs[0][lds_off[s]]) = rb_reg[s];
-    }
-    __syncthreads();
-
-    const int half = lane >> 5;
-    for (int64_t kt = 0; kt < nk; ++kt) {
-        const int buf = (int)(kt & 1);
-        if (kt + 1 < nk) {
-#pragma unroll
-            for (int s = 0; s < LOADS; ++s) {
-                ra_reg[s] = *reinterpret_cast<const uint4 *>(ga[s] + (kt + 1) * RB);
-                rb_reg[s] = *reinterpret_cast<const uint4 *>(gb[s] + (kt + 1) * RB);
-            }
-        }
-        uint32_t swa[2], swb[2];
-#pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            swa[i] = *reinterpret_cast<const uint32_t *>(sa_row[i] + kt * (g.a1d ? g.ldsa : 4));
-            swb[i] = *reinterpret_cast<const uint32_t *>(sb_row[i] + kt * (g.b1d ? g.ldsb : 4));
-        }
-#pragma unroll
-        for (int ks = 0; ks < 2; ++ks) {
-            v8i af[2], bf[2];
-            int sa[2], sb[2];
-            const int kg = 2 * ks + half;
-#pragma unroll
-            for (int i = 0; i < 2; ++i) {
-                const int ra = wm * 64 + i * 32 + (lane & 31);
-                const int rb = wn * 64 + i * 32 + (lane & 31);
-#pragma unroll
-                for (int h = 0; h < F::kLaneBytes / 16; ++h) {
-                    const int ch = F::chunk(ks, half, h);
-                    const uint4 qa = *reinterpret_cast<const uint4 *>(&As[buf][ra * RB + ((ch ^ F::swz(ra)) * 16)]);
-                    const uint4 qb = *reinterpret_cast<const uint4 *>(&Bs[buf][rb * RB + ((ch ^ F::swz(rb)) * 16)]);
-                    af[i][4 * h + 0] = (int)qa.x; af[i][4 * h + 1] = (int)qa.y;
-                    af[i][4 * h + 2] = (int)qa.z; af[i][4 * h + 3] = (int)qa.w;
-                    bf[i][4 * h + 0] = (int)qb.x; bf[i][4 * h + 1] = (int)qb.y;
-                    bf[i][4 * h + 2] = (int)qb.z; bf[i][4 * h + 3] = (int)qb.w;
-                }
-                if (F::kLaneBytes == 16) {
-#pragma unroll
-                    for (int z = 4; z < 8; ++z) { af[i][z] = 0; bf[i][z] = 0; }
-                }
-                sa[i] = (int)((swa[i] >> (8 * kg)) & 0xFFu);
-                sb[i] = (int)((swb[i] >> (8 * kg)) & 0xFFu);
-            }
-#pragma unroll
-            for (int i = 0; i < 2; ++i)
-#pragma unroll
-                for (int j = 0; j < 2; ++j)
-                    acc[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(
-                        af[i], bf[j], acc[i][j], F::kCbsz, F::kCbsz, 0, sa[i], 0, sb[j]);
-        }
-        if (kt + 1 < nk) {
-#pragma unroll
-            for (int s = 0; s < LOADS; ++s) {
-                *reinterpret_cast<uint4 *>(&As[buf ^ 1][lds_off[s]]) = ra_reg[s];
-                *reinterpret_cast<uint4 *>(&Bs[buf ^ 1][lds_off[s]]) = rb_reg[s];
-            }
-        }
-        __syncthreads();
-    }
-
-    // ---- epilogue: lane holds column (lane % 32) and rows 8*(r/4) + 4*(lane/32) + r%4
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j) {
-            const int64_t col = n0 + wn * 64 + j * 32 + (lane & 31);
-            if (col >= g.N) continue;
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int64_t row = m0 + wm * 64 + i * 32 + 8 * (r >> 2) + 4 * half + (r & 3);
-                if (row >= g.M) continue;
-                float v = acc[i][j][r];
-                if (BF16OUT) {
-                    uint16_t *p = reinterpret_cast<uint16_t *>(g.c) + row * g.ldc + col;
-                    if (g.accumulate) v += bf16_to_f(*p);
-                    *p = f_to_bf16_rne(v);
-                } else {
-                    float *p = reinterpret_cast<float *>(g.c) + row * g.ldc + col;
-                    if (g.accumulate) v += *p;
-                    *p = v;
-                }
-            }
-        }
-}
 
 // Large-tile FP4 kernel: 256 x 256 output tile, 4 waves of 128 x 128 (4 x 4
 // MFMA tiles, 256 fp32 accumulators per lane held in AGPRs), one wave per
@@ -281,34 +57,6 @@ constexpr int BM2 = 256, BN2 = 256;
 constexpr int kStages = 4;
 constexpr int kDmaPerTile = 9;      // per wave: 4 for A, 4 for B, 1 for the scale words
 constexpr int kCodeBytes = BM2 * 64;                  // 16 KB per operand per stage
-
-// Wave-uniform 64-bit value (moves it to SGPRs).
-__device__ __forceinline__ uint64_t uniform64(uint64_t v)
-{
-    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v);
-    const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
-    return ((uint64_t)hi << 32) | lo;
-}
-
-// global -> LDS, 16 bytes per lane at M0 + 16 * lane; address = sbase + voff
-// with a wave-uniform base
-__device__ __forceinline__ void lds_dma16(const uint8_t *sbase, uint32_t voff, uint32_t lds_addr)
-{
-    const uint64_t base = uniform64(reinterpret_cast<uint64_t>(sbase));
-    asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds_addr), "v"(voff), "s"(base)
-                 : "memory");
-}
-
-// global -> LDS, 4 bytes per lane at M0 + 4 * lane, per-lane 64-bit address
-__device__ __forceinline__ void lds_dma4(const uint8_t *src, uint32_t lds_addr)
-{
-    asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dword %1, off" ::"s"(lds_addr), "v"(src) : "memory");
-}
-
-template <int N>
-__device__ __forceinline__ void wait_vmcnt() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
-
-__device__ __forceinline__ void block_barrier() { asm volatile("s_barrier" ::: "memory"); }
 
 // Write a wave's 128 x 128 accumulator block (4 x 4 MFMA tiles) to C; CHECK
 // masks rows >= M and columns >= N.  bf16 output rounds to nearest even.  The
@@ -419,7 +167,7 @@ struct TileSpace {
         t.M = (int32_t)g.M; t.N = (int32_t)g.N; t.nk = (uint32_t)(g.K / BK);
         int32_t tm, tn;
         if (GMODE == 0) {
-            // as tile_coords, in 32 bits
+            // as tile_coords_of, in 32 bits
             const uint32_t xcd = u % kXcds, local = u / kXcds;
             const uint32_t tt = xcd * per + (xcd < rem ? xcd : rem) + local;
             const uint32_t grp = tt / span, first = grp * kGroupM;
@@ -575,14 +323,6 @@ __device__ __forceinline__ void store_block_pairs(v16f (&acc)[4][4], uint8_t *cb
         }
 }
 
-// Row of B (within a 256-row tile) that feeds MFMA row slot t = 128 h + 32 j + l
-// of the interleaved-column layout: 128 h + 64 (j / 2) + 2 l + j % 2.
-__device__ __forceinline__ int interleaved_row(int t)
-{
-    const int j = (t >> 5) & 3, l = t & 31;
-    return (t & ~127) + 64 * (j >> 1) + 2 * l + (j & 1);
-}
-
 // Quantize a wave's 128 x 128 accumulator block into 2D-block FP4 with round to
 // nearest (the quantizer's scale rule and codec, applied to the float32
 // result): each 32 x 32 MFMA tile is exactly one block.
@@ -611,18 +351,6 @@ __device__ __forceinline__ int interleaved_row(int t)
 // Philox block covers 8 consecutive columns of one row: the wave computes each
 // of a tile's 128 blocks once (two per lane) into its LDS table, and every lane
 // reads back the 16-bit draws of the 16 elements it holds.
-// f(std::integral_constant<int, 0>) ... f(std::integral_constant<int, N - 1>), in order
-template <typename F, int... Is>
-__device__ __forceinline__ void unroll_seq(F &&f, std::integer_sequence<int, Is...>)
-{
-    (f(std::integral_constant<int, Is>{}), ...);
-}
-template <int N, typename F>
-__device__ __forceinline__ void unroll(F &&f)
-{
-    unroll_seq(f, std::make_integer_sequence<int, N>{});
-}
-
 constexpr int kQPitch = 80;                     // LDS strip row pitch (64 bytes + pad)
 constexpr int kQStrip = 32 * kQPitch;           // per wave
 constexpr int kPRow = 80;                       // Philox table row: four 16-byte blocks + pad
@@ -824,7 +552,7 @@ __global__ __launch_bounds__(kThreads, 1) void gemm_fp4_persistent_kernel(GemmAr
                                                                           const GroupedArgs gr)
 {
     using F = Fmt<kFmtFp4Block2D>;
-    constexpr int RB = F::kRowBytes;                // 64
+    constexpr int RB = 64;                          // code bytes per row per K-tile
     constexpr bool A1 = (SM & 1) != 0, B1 = (SM & 2) != 0;
     constexpr int kDma = kDmaPerTile + A1 + B1;     // 9 .. 11
     constexpr int kWordsA1 = 2 * kCodeBytes + 1024;             // after 2 x codes + 1 KB of 2D scale words: per-row A scale words
@@ -934,7 +662,7 @@ __global__ __launch_bounds__(kThreads, 1) void gemm_fp4_persistent_kernel(GemmAr
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
         row[j] = 16 * (4 * j + wave) + (lane >> 2);
-        c16[j] = ((lane & 3) ^ F::swz(row[j])) * 16;
+        c16[j] = ((lane & 3) ^ swz(row[j])) * 16;
     }
     const int sq = lane & 7;                        // scale words: 0-3 A block rows, 4-7 B block rows
     const int srow = sq < 4 ? wm * 128 + sq * 32 : wn * 128 + (sq - 4) * 32;
@@ -1018,7 +746,7 @@ __global__ __launch_bounds__(kThreads, 1) void gemm_fp4_persistent_kernel(GemmAr
         }
     };
 
-    const int sw = F::swz(lane & 31);
+    const int sw = swz(lane & 31);
     const int rd_a = (wm * 128 + (lane & 31)) * RB;
     const int rd_b = kCodeBytes + (wn * 128 + (lane & 31)) * RB;
     uint4 fa0[4], fb0[4], fa1[4], fb1[4];
@@ -1159,7 +887,7 @@ __global__ __launch_bounds__(kThreads, 1) void gemm_fp8_256_kernel(GemmArgs g, i
     int tm, tn;
     {
         int64_t tm64, tn64;
-        tile_coords(tiles_m, tiles_n, tm64, tn64);
+        tile_coords_of<int64_t>(blockIdx.x, tiles_m, tiles_n, kGroupM, tm64, tn64);
         tm = (int)tm64; tn = (int)tn64;
     }
     const int64_t m0 = (int64_t)tm * BM2, n0 = (int64_t)tn * BN2;
@@ -1181,7 +909,7 @@ __global__ __launch_bounds__(kThreads, 1) void gemm_fp8_256_kernel(GemmArgs g, i
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
         const int row = 16 * (4 * j + wave) + (lane >> 2);
-        const int c = (lane & 3) ^ Fmt<kFmtFp4Block2D>::swz(row);
+        const int c = (lane & 3) ^ swz(row);
         int64_t ra = m0 + row; ra = ra < g.M ? ra : g.M - 1;
         int64_t rb = n0 + (PERM ? interleaved_row(row) : row); rb = rb < g.N ? rb : g.N - 1;
         offA[j] = (uint32_t)(ra * g.lda + c * 16);
@@ -1196,7 +924,7 @@ __global__ __launch_bounds__(kThreads, 1) void gemm_fp8_256_kernel(GemmArgs g, i
         soffB = (uint32_t)(rb * g.ldsb);
     }
     const uint32_t lds0 = (uint32_t)(uintptr_t)&smem[0];
-    const int sw = Fmt<kFmtFp4Block2D>::swz(lane & 31);
+    const int sw = swz(lane & 31);
     const int rd_a = (wm * 128 + (lane & 31)) * RB;
     const int rd_b = kCodeBytes + (wn * 128 + (lane & 31)) * RB;
     // the lane's row words: word path at stage + 2 * kCodeBytes (+ 1024 for B);
@@ -1416,53 +1144,40 @@ hipError_t launch_dense(const GemmArgs &g, int tm, int tn, hipStream_t s)
     }
 }
 
-template <int FMT, bool BF>
-hipError_t launch_t(const GemmArgs &g, hipStream_t s)
-{
-    const int64_t tm = (g.M + BM - 1) / BM, tn = (g.N + BN - 1) / BN;
-    hipLaunchKernelGGL((gemm_kernel<FMT, BF>), dim3((unsigned)(tm * tn)), dim3(kThreads), 0, s, g, tm, tn);
-    return hipGetLastError();
-}
-
 }  // namespace
 
 hipError_t launch_gemm(const GemmArgs &g, int fmt, int c_is_bf16, hipStream_t stream)
 {
-    // the 256 x 256 kernel once there are enough output tiles to fill the chip
-    // (its loads address each operand with 32-bit byte offsets from the K-tile base)
+    // the 256 x 256 kernels address each operand with 32-bit byte offsets from the
+    // K-tile base
     const bool off32 = g.M * g.lda <= (int64_t(1) << 32) && g.N * g.ldb <= (int64_t(1) << 32);
-    if (fmt == kFmtFp4Block2D && off32 && ((g.M + BM2 - 1) / BM2) * ((g.N + BN2 - 1) / BN2) >= 128) {
-        const int tm = (int)((g.M + BM2 - 1) / BM2), tn = (int)((g.N + BN2 - 1) / BN2);
-        return c_is_bf16 ? launch_dense<true>(g, tm, tn, stream) : launch_dense<false>(g, tm, tn, stream);
-    }
+    const SmallTile tile = pick_tile(g, fmt, off32);
+    if (tile != kTile256) return launch_gemm_small(g, fmt, c_is_bf16, tile, stream);
+    const int tm = (int)((g.M + BM2 - 1) / BM2), tn = (int)((g.N + BN2 - 1) / BN2);
     if (fmt == kFmtFp4Block2D)
-        return c_is_bf16 ? launch_t<kFmtFp4Block2D, true>(g, stream) : launch_t<kFmtFp4Block2D, false>(g, stream);
-    if (off32 && ((g.M + BM2 - 1) / BM2) * ((g.N + BN2 - 1) / BN2) >= 128) {
-        const int tm = (int)((g.M + BM2 - 1) / BM2), tn = (int)((g.N + BN2 - 1) / BN2);
-        // 16-byte scale loads: whole groups of 8 K-tiles, 16-byte aligned rows
-        const bool s16 = g.K % 512 == 0 && g.ldsa % 16 == 0 && g.ldsb % 16 == 0 &&
-                         reinterpret_cast<uintptr_t>(g.sa) % 16 == 0 && reinterpret_cast<uintptr_t>(g.sb) % 16 == 0;
-        const dim3 grid((unsigned)(tm * tn)), block(kThreads);
-        if (s16) {
-            if (c_is_bf16) {
-                if (g.accumulate) hipLaunchKernelGGL((gemm_fp8_256_kernel<true, true, true>), grid, block, 0, stream, g, tm, tn);
-                else hipLaunchKernelGGL((gemm_fp8_256_kernel<true, false, true>), grid, block, 0, stream, g, tm, tn);
-            } else {
-                if (g.accumulate) hipLaunchKernelGGL((gemm_fp8_256_kernel<false, true, true>), grid, block, 0, stream, g, tm, tn);
-                else hipLaunchKernelGGL((gemm_fp8_256_kernel<false, false, true>), grid, block, 0, stream, g, tm, tn);
-            }
+        return c_is_bf16 ? launch_dense<true>(g, tm, tn, stream) : launch_dense<false>(g, tm, tn, stream);
+    // 16-byte scale loads: whole groups of 8 K-tiles, 16-byte aligned rows
+    const bool s16 = g.K % 512 == 0 && g.ldsa % 16 == 0 && g.ldsb % 16 == 0 &&
+                     reinterpret_cast<uintptr_t>(g.sa) % 16 == 0 && reinterpret_cast<uintptr_t>(g.sb) % 16 == 0;
+    const dim3 grid((unsigned)(tm * tn)), block(kThreads);
+    if (s16) {
+        if (c_is_bf16) {
+            if (g.accumulate) hipLaunchKernelGGL((gemm_fp8_256_kernel<true, true, true>), grid, block, 0, stream, g, tm, tn);
+            else hipLaunchKernelGGL((gemm_fp8_256_kernel<true, false, true>), grid, block, 0, stream, g, tm, tn);
         } else {
-            if (c_is_bf16) {
-                if (g.accumulate) hipLaunchKernelGGL((gemm_fp8_256_kernel<true, true, false>), grid, block, 0, stream, g, tm, tn);
-                else hipLaunchKernelGGL((gemm_fp8_256_kernel<true, false, false>), grid, block, 0, stream, g, tm, tn);
-            } else {
-                if (g.accumulate) hipLaunchKernelGGL((gemm_fp8_256_kernel<false, true, false>), grid, block, 0, stream, g, tm, tn);
-                else hipLaunchKernelGGL((gemm_fp8_256_kernel<false, false, false>), grid, block, 0, stream, g, tm, tn);
-            }
+            if (g.accumulate) hipLaunchKernelGGL((gemm_fp8_256_kernel<false, true, true>), grid, block, 0, stream, g, tm, tn);
+            else hipLaunchKernelGGL((gemm_fp8_256_kernel<false, false, true>), grid, block, 0, stream, g, tm, tn);
         }
-        return hipGetLastError();
+    } else {
+        if (c_is_bf16) {
+            if (g.accumulate) hipLaunchKernelGGL((gemm_fp8_256_kernel<true, true, false>), grid, block, 0, stream, g, tm, tn);
+            else hipLaunchKernelGGL((gemm_fp8_256_kernel<true, false, false>), grid, block, 0, stream, g, tm, tn);
+        } else {
+            if (g.accumulate) hipLaunchKernelGGL((gemm_fp8_256_kernel<false, true, false>), grid, block, 0, stream, g, tm, tn);
+            else hipLaunchKernelGGL((gemm_fp8_256_kernel<false, false, false>), grid, block, 0, stream, g, tm, tn);
+        }
     }
-    return c_is_bf16 ? launch_t<kFmtMxfp8, true>(g, stream) : launch_t<kFmtMxfp8, false>(g, stream);
+    return hipGetLastError();
 }
 
 namespace {

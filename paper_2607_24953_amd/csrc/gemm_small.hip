@@ -1,0 +1,612 @@
+// Block-scaled GEMMs with few output tiles: C[M][N] (+)= A . B^T as in gemm.hip
+// (FP4 with 2D or 1D blocks, MXFP8), on tiles small enough to fill the chip.
+//
+// Both kernels stage XOR-swizzled operand rows in LDS with the global -> LDS loads
+// of the large-tile kernels.
+//
+// gemm_tile_kernel: 128 x 128 or 256 x 128 tiles, 2 x 2 waves, a ring of three
+// stages shared by the workgroup.  What bounds it: at 256 workgroups the loads --
+// an L2 channel serves one request a cycle whether it is 64 or 128 bytes, so
+// stages hold whole 128-byte lines (with 64-byte rows a stage of 128 values took
+// 920 cycles against 650-720 on 2048 x 4096 x 4096), and a load instruction costs
+// the CU 16-20 cycles whatever its size, so 2D scale words come with one load per
+// wave and stage.  Alone on a CU it is bound by its own issue: the next fragments'
+// reads and the loads sit between MFMAs (all loads in one group: 14.4 us for 128 x
+// 4096 x 4096, spread 10.9 us).
+//
+// gemm_ksplit_kernel: 32 x 32 or 64 x 64 tiles; the four waves of a workgroup
+// split K.  Each wave runs its own ring (64-byte rows, four stages, a scale word
+// per row) over its K range, so the K loop has no barrier, and the partial tiles
+// meet in LDS at the end, added in wave order (the result does not depend on
+// timing).  It is bound by load latency and, from a few hundred tiles on, by the
+// operand bytes each small tile loads for itself.
+//
+// Before these kernels a 128 x 128 register-staged kernel took 47.9 us for 16 x
+// 12288 x 4096 (now 8.0), 34 us for 2000 x 2048 x 2048 (11.2), 8 us for 128 x 256
+// x 256 (2.9), kernel trace against launches in a graph.
+#include "gemm_common.hpp"
+
+namespace q2d {
+
+namespace {
+
+constexpr int kRing = 4;                        // stages of gemm_ksplit_kernel's rings
+
+struct Frag {
+    uint4 q0, q1;                               // chunks h and 2 + h of the row's 64 bytes
+    uint32_t w;                                 // the row's scale word
+};
+
+// row r of a stage (WORD: with its scale word)
+template <bool WORD>
+__device__ __forceinline__ void read_frag(Frag &f, const uint8_t *rows, const uint8_t *words, int r, int half)
+{
+    const int sw = swz(r);
+    f.q0 = *reinterpret_cast<const uint4 *>(rows + r * 64 + ((half ^ sw) * 16));
+    f.q1 = *reinterpret_cast<const uint4 *>(rows + r * 64 + (((2 + half) ^ sw) * 16));
+    if (WORD) f.w = *reinterpret_cast<const uint32_t *>(words + r * 4);
+}
+
+// Product ks of a stage for a 32-row A fragment and a 32-row B fragment (E2M1:
+// two products of 64 values; E4M3: one).  wa, wb: the scale words shifted right
+// by 8 * half, so that bytes 0 and 2 belong to this lane half.  E4M3: PAR is the
+// stage's half of the 128 values of its word.
+template <int FMT, int PAR, int KS>
+__device__ __forceinline__ void mfma_stage(v16f &acc, const Frag &a, const Frag &b, uint32_t wa, uint32_t wb)
+{
+    constexpr int C = Fmt<FMT>::kCbsz;
+    if constexpr (FMT == kFmtFp4Block2D) {
+        const uint4 qa = KS ? a.q1 : a.q0, qb = KS ? b.q1 : b.q0;
+        const v8i av = {(int)qa.x, (int)qa.y, (int)qa.z, (int)qa.w, 0, 0, 0, 0};
+        const v8i bv = {(int)qb.x, (int)qb.y, (int)qb.z, (int)qb.w, 0, 0, 0, 0};
+        acc = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(av, bv, acc, C, C, 2 * KS, (int)wa, 2 * KS, (int)wb);
+    } else {
+        const v8i av = {(int)a.q0.x, (int)a.q0.y, (int)a.q0.z, (int)a.q0.w,
+                        (int)a.q1.x, (int)a.q1.y, (int)a.q1.z, (int)a.q1.w};
+        const v8i bv = {(int)b.q0.x, (int)b.q0.y, (int)b.q0.z, (int)b.q0.w,
+                        (int)b.q1.x, (int)b.q1.y, (int)b.q1.z, (int)b.q1.w};
+        acc = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(av, bv, acc, C, C, 2 * PAR, (int)wa, 2 * PAR, (int)wb);
+    }
+}
+
+// The MFMAs of one stage, with the next stage's fragment reads (read(k), k < TI +
+// TJ: A fragments, then B) and the loads into the freed slot (load(k), k < LOADS)
+// spread between them (a wave issues in order, and a global -> LDS load may wait
+// for the ones before it: back to back they would hold up the MFMAs behind them);
+// sched_barrier pins the order.
+template <int FMT, int PAR, int TI, int TJ, int LOADS, typename RD, typename LD>
+__device__ __forceinline__ void stage_products(v16f (&acc)[TI][TJ], const Frag (&fa)[TI], const Frag (&fb)[TJ], int half,
+                                               RD &&read, LD &&load)
+{
+    constexpr int KS = FMT == kFmtFp4Block2D ? 2 : 1, NM = KS * TI * TJ, NR = TI + TJ, NI = NR + LOADS;
+    uint32_t wa[TI], wb[TJ];
+#pragma unroll
+    for (int i = 0; i < TI; ++i) wa[i] = fa[i].w >> (8 * half);
+#pragma unroll
+    for (int j = 0; j < TJ; ++j) wb[j] = fb[j].w >> (8 * half);
+    unroll<NM>([&](auto mc) __attribute__((always_inline)) {
+        constexpr int m = decltype(mc)::value, ks = m / (TI * TJ), i = m / TJ % TI, j = m % TJ;
+        mfma_stage<FMT, PAR, ks>(acc[i][j], fa[i], fb[j], wa[i], wb[j]);
+        __builtin_amdgcn_sched_barrier(0);
+        constexpr int k0 = m * NI / NM, k1 = (m + 1) * NI / NM;
+        unroll<k1 - k0>([&](auto kc) __attribute__((always_inline)) {
+            constexpr int k = k0 + decltype(kc)::value;
+            if constexpr (k < NR) read(std::integral_constant<int, k>{});
+            else load(std::integral_constant<int, k - NR>{});
+        });
+        __builtin_amdgcn_sched_barrier(0);
+    });
+}
+
+// Scale word of operand row r for stage t at scales + word_row(r) + t * step: 2D
+// blocks: grid row r / 32, step 4; 1D blocks: K-tile-major words, step ld; MXFP8:
+// one word per row and two stages, step 4 for two.
+template <int FMT>
+__device__ __forceinline__ int64_t word_row(int64_t r, int64_t ld, bool oned)
+{
+    if (FMT == kFmtMxfp8) return r * ld;
+    return oned ? 4 * r : (r >> 5) * ld;
+}
+
+// gemm_ksplit_kernel's wait in the body of stage s: the next stage has landed.  left: stages
+// after s (as many as the ring holds are in flight).  CODES and WORDS: this wave's
+// loads of codes and of scale words; MXFP8 stages bring words only where their
+// number is even (PAR: s's parity).
+template <int FMT, int PAR, int CODES, int WORDS>
+__device__ __forceinline__ void wait_next(uint32_t left)
+{
+    constexpr bool F8 = FMT == kFmtMxfp8;
+    static_assert(kRing == 4, "two stages may stay in flight behind the next one");
+    if (left >= 3) wait_vmcnt<2 * CODES + (F8 ? 1 : 2) * WORDS>();
+    else if (left == 2) wait_vmcnt<CODES + (F8 && PAR ? 0 : WORDS)>();
+    else wait_vmcnt<0>();
+}
+// the same before the first stage: n stages in all
+template <int FMT, int CODES, int WORDS>
+__device__ __forceinline__ void wait_first(uint32_t n)
+{
+    constexpr bool F8 = FMT == kFmtMxfp8;
+    if (n >= 4) wait_vmcnt<3 * CODES + (F8 ? 1 : 3) * WORDS>();
+    else if (n == 3) wait_vmcnt<2 * CODES + (F8 ? 1 : 2) * WORDS>();
+    else if (n == 2) wait_vmcnt<CODES + (F8 ? 0 : WORDS)>();
+    else wait_vmcnt<0>();
+}
+
+typedef __bf16 bf2_t __attribute__((ext_vector_type(2)));
+
+// bf16 output: interleaved columns (MFMA tiles 2 p and 2 p + 1 of a wave take B
+// rows 64 p + 2 l and 64 p + 2 l + 1), so that a lane holds neighbouring columns
+// and 32 lanes store a 128-byte run; pair stores need C and its pitch aligned.
+__device__ __forceinline__ bool pair_stores(const GemmArgs &g)
+{
+    return ((reinterpret_cast<uintptr_t>(g.c) | (uintptr_t)(g.ldc * 2)) & 3u) == 0;
+}
+
+// One element of C
+template <bool BF16OUT>
+__device__ __forceinline__ void store_one(const GemmArgs &g, int64_t row, int64_t col, float v)
+{
+    if (BF16OUT) {
+        __bf16 *p = reinterpret_cast<__bf16 *>(g.c) + row * g.ldc + col;
+        *p = (__bf16)(g.accumulate ? v + (float)*p : v);
+    } else {
+        float *p = reinterpret_cast<float *>(g.c) + row * g.ldc + col;
+        *p = g.accumulate ? v + *p : v;
+    }
+}
+
+// 16-byte chunk swizzle of 128-byte LDS rows, conflict-free for the fragment
+// reads: the four rows read together with both lane halves map to distinct chunk
+// pairs, and eight consecutive rows to distinct chunks
+__device__ __forceinline__ int swz128(int r)
+{
+    return ((r & 2) << 1) | (((r ^ (r >> 3)) & 1) << 1) | ((r >> 2) & 1);
+}
+
+// (64 TI) x (64 TJ) tiles, each wave (32 TI) x (32 TJ); RING stages of 128-byte
+// operand rows (256 E2M1 or 128 E4M3 values), i.e. two units of 64 bytes.  A unit
+// is the MFMAs on one set of fragments while the next unit's are read; the loads
+// of stage s + RING go out over the second unit of stage s and the first of
+// stage s + 1.  WM: how the scale words come: 0 -- both operands in 2D blocks: each
+// wave loads its own block rows' words of both units at once; 1 -- one word per
+// row (1D blocks, MXFP8).
+template <int FMT, int TI, int TJ, int RING, int WM, bool BF16OUT>
+__global__ __launch_bounds__(kThreads, 1) void gemm_tile_kernel(const GemmArgs g, uint32_t tiles_m, uint32_t tiles_n)
+{
+    constexpr bool F8 = FMT == kFmtMxfp8;
+    constexpr int TM = 64 * TI, TN = 64 * TJ, kRows = TM + TN;
+    constexpr int kWords = 128 * kRows;                         // byte offset of the scale words in a stage
+    constexpr int WU = F8 ? 1 : 2;                              // scale words per row and stage
+    constexpr int WG = WM ? (kRows / 64 + 3) / 4 : 1;           // 64-row word groups per wave
+    constexpr int kStage = kWords + (WM ? 4 * WU * kRows : 4 * 256);
+    constexpr int CODES = kRows / 32, WORDS = WM ? WU * WG : 1; // this wave's loads per stage
+    constexpr int LOADS = CODES + WORDS, H1 = (LOADS + 1) / 2;  // the first H1 in the second unit
+    static_assert(WM || !F8, "MXFP8 has one word per row");
+    __shared__ __attribute__((aligned(1024))) uint8_t smem[RING * kStage];
+
+    uint32_t tm, tn;
+    tile_coords_of(blockIdx.x, tiles_m, tiles_n, 8u, tm, tn);
+    const int64_t m0 = (int64_t)tm * TM, n0 = (int64_t)tn * TN;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wm = wave >> 1, wn = wave & 1, half = lane >> 5;
+    const uint32_t nu = (uint32_t)(g.K / Fmt<FMT>::kStepK);     // units (MXFP8: an even number)
+    const uint32_t ns = (nu + 1) / 2;                           // stages
+
+    // operand row of the stage's row t: A rows, then B rows (clamped into the operand)
+    auto row_of = [&](int t) __attribute__((always_inline)) -> int64_t {
+        const int tb = t - TM;
+        const int64_t r = t < TM ? m0 + t : n0 + (BF16OUT ? interleaved_row(tb) : tb);
+        const int64_t lim = t < TM ? g.M : g.N;
+        return r < lim ? r : lim - 1;
+    };
+    const uint8_t *pc[CODES], *pw[WORDS];
+#pragma unroll
+    for (int k = 0; k < CODES; ++k) {
+        const int t = 32 * k + 8 * wave + (lane >> 3), c16 = ((lane & 7) ^ swz128(t)) * 16;
+        pc[k] = (32 * k < TM ? g.a + row_of(t) * g.lda : g.b + row_of(t) * g.ldb) + c16;
+    }
+    // the last stage of an odd number of units: its second half does not exist (rows
+    // t and t + 32 k have the same swizzle, so this holds for every load)
+    const int back = ((lane & 7) ^ swz128(8 * wave + (lane >> 3))) >= 4 ? 64 : 0;
+    int64_t wstep[WG];                                          // bytes per unit (MXFP8: per stage)
+    int wgrp[WG];
+    if constexpr (WM == 0) {
+        // lane: unit lane / 32, block row lane % 32 of the wave's TI + TJ (clamped)
+        const int x = (lane & 31) < TI + TJ ? (lane & 31) : TI + TJ - 1;
+        const bool is_a = x < TI;
+        int64_t r = is_a ? m0 + wm * 32 * TI + 32 * x : n0 + wn * 32 * TJ + 32 * (x - TI);
+        const int64_t lim = is_a ? g.M : g.N;
+        r = r < lim ? r : lim - 1;
+        pw[0] = (is_a ? g.sa : g.sb) + (r >> 5) * (is_a ? g.ldsa : g.ldsb) + 4 * half;
+        wgrp[0] = wave; wstep[0] = 4;
+    } else {
+        // 64-row groups wave, 4 + wave % 2; a group belongs to one operand
+#pragma unroll
+        for (int k = 0; k < WG; ++k) {
+            wgrp[k] = k == 0 ? wave : 4 + (wave & 1);
+            const bool is_a = wgrp[k] < TI;
+            const bool oned = is_a ? g.a1d : g.b1d;
+            const int64_t ld = is_a ? g.ldsa : g.ldsb;
+            wstep[k] = !F8 && oned ? ld : 4;
+            pw[k] = (is_a ? g.sa : g.sb) + word_row<FMT>(row_of(64 * wgrp[k] + lane), ld, oned);
+        }
+    }
+    const uint32_t lds0 = (uint32_t)(uintptr_t)&smem[0];
+    // load k of stage s: codes, then scale words (past the last stage: that one
+    // again, into a slot that is not read any more)
+    auto load = [&](uint32_t s, uint32_t slot, int k) __attribute__((always_inline)) {
+        const uint32_t stage = lds0 + slot * kStage;
+        const uint32_t t = s < ns ? s : ns - 1;
+        const bool cut = !F8 && 2 * t + 1 >= nu;                // only the first unit exists
+        if (k < CODES) {
+            const uint8_t *p = pc[k < CODES ? k : 0] + (uint64_t)t * 128;
+            lds_dma16(cut ? p - back : p, stage + (4 * k + wave) * 1024);
+        } else if (WM == 0) {
+            const uint8_t *p = pw[0] + (uint64_t)t * 8;
+            lds_dma4(cut && half ? p - 4 : p, stage + kWords + wave * 256);
+        } else {
+            const int w = k < CODES ? 0 : k - CODES, u = w / WG, gi = w % WG;
+            const uint32_t ut = F8 ? t : (cut ? 2 * t : 2 * t + u);
+            lds_dma4(pw[gi] + ut * wstep[gi], stage + kWords + u * (4 * kRows) + wgrp[gi] * 256);
+        }
+    };
+
+    v16f acc[TI][TJ];
+#pragma unroll
+    for (int i = 0; i < TI; ++i)
+#pragma unroll
+        for (int j = 0; j < TJ; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
+
+    Frag fa0[TI], fb0[TJ], fa1[TI], fb1[TJ];
+    const int sw = swz128(lane & 31);
+    // fragment k of unit u of the stage in `slot` (MXFP8: the scale words come with unit 0)
+    auto read = [&](auto uc, uint32_t slot, int k, Frag (&fa)[TI], Frag (&fb)[TJ]) __attribute__((always_inline)) {
+        constexpr int u = decltype(uc)::value;
+        const uint8_t *st = smem + slot * kStage;
+        const int r = (k < TI ? (wm * TI + k) * 32 : TM + (wn * TJ + k - TI) * 32) + (lane & 31);
+        Frag &f = k < TI ? fa[k < TI ? k : 0] : fb[k < TI ? 0 : k - TI];
+        f.q0 = *reinterpret_cast<const uint4 *>(st + r * 128 + (((4 * u + half) ^ sw) * 16));
+        f.q1 = *reinterpret_cast<const uint4 *>(st + r * 128 + (((4 * u + 2 + half) ^ sw) * 16));
+        if constexpr (WM == 0) {
+            // bf16: the interleaved B rows of lanes 0..15 and 16..31 lie in different blocks
+            const int x = k < TI ? k : TI + (BF16OUT ? 2 * ((k - TI) >> 1) + ((lane & 31) >> 4) : k - TI);
+            f.w = *reinterpret_cast<const uint32_t *>(st + kWords + wave * 256 + u * 128 + 4 * x);
+        } else if constexpr (!F8 || u == 0) {
+            f.w = *reinterpret_cast<const uint32_t *>(st + kWords + (F8 ? 0 : u) * (4 * kRows) + 4 * r);
+        }
+    };
+
+    // stages 0 .. RING - 2 and the first part of stage RING - 1
+#pragma unroll
+    for (uint32_t t = 0; t < RING; ++t)
+#pragma unroll
+        for (int k = 0; k < (t + 1 < RING ? LOADS : H1); ++k) load(t, t, k);
+    wait_vmcnt<(RING - 2) * LOADS + H1>();
+    block_barrier();
+#pragma unroll
+    for (int k = 0; k < TI + TJ; ++k) read(std::integral_constant<int, 0>{}, 0, k, fa0, fb0);
+    // the second unit's fragments of the stage in `slot` (MXFP8: the first's words)
+    auto read1 = [&](uint32_t slot, int k) __attribute__((always_inline)) {
+        read(std::integral_constant<int, 1>{}, slot, k, fa1, fb1);
+        if constexpr (F8) {
+            if (k < TI) fa1[k < TI ? k : 0].w = fa0[k < TI ? k : 0].w;
+            else fb1[k < TI ? 0 : k - TI].w = fb0[k < TI ? 0 : k - TI].w;
+        }
+    };
+
+    uint32_t slot = 0, prev = RING - 1;                         // s % RING, (s - 1) % RING
+    for (uint32_t s = 0; s + 1 < ns; ++s) {
+        const uint32_t next = slot + 1 == RING ? 0 : slot + 1;
+        // ---- unit 0; the second part of the loads of stage s - 1 + RING
+        wait_lgkm();
+        stage_products<FMT, 0, TI, TJ, LOADS - H1>(
+            acc, fa0, fb0, half, [&](auto k) __attribute__((always_inline)) { read1(slot, k); },
+            [&](auto k) __attribute__((always_inline)) { load(s - 1 + RING, prev, H1 + k); });
+        wait_lgkm();                                    // this wave has read stage s
+        wait_vmcnt<(RING - 2) * LOADS>();               // its loads of stage s + 1 have landed
+        block_barrier();
+        // ---- unit 1; the first part of the loads of stage s + RING
+        stage_products<FMT, 1, TI, TJ, H1>(
+            acc, fa1, fb1, half,
+            [&](auto k) __attribute__((always_inline)) { read(std::integral_constant<int, 0>{}, next, k, fa0, fb0); },
+            [&](auto k) __attribute__((always_inline)) { load(s + RING, slot, k); });
+        prev = slot;
+        slot = next;
+    }
+    // ---- the last stage: one or two units
+    wait_lgkm();
+    stage_products<FMT, 0, TI, TJ, 0>(acc, fa0, fb0, half, [&](auto k) __attribute__((always_inline)) { read1(slot, k); },
+                                      [](auto) {});
+    if (F8 || (nu & 1) == 0) {
+        wait_lgkm();
+        stage_products<FMT, 1, TI, TJ, 0>(acc, fa1, fb1, half, [](auto) {}, [](auto) {});
+    }
+    wait_vmcnt<0>();                                    // nothing lands in LDS from here on
+
+    // a lane holds column lane % 32 (bf16: a pair) and rows 8 q + 4 half + 0..3 of
+    // every MFMA tile
+    const int64_t r0 = m0 + wm * 32 * TI, c0 = n0 + wn * 32 * TJ;
+    if (m0 + TM <= g.M && n0 + TN <= g.N && !g.accumulate && (!BF16OUT || pair_stores(g))) {
+        uint8_t *p = reinterpret_cast<uint8_t *>(g.c) + ((r0 + 4 * half) * g.ldc + c0) * (BF16OUT ? 2 : 4) + 4 * (lane & 31);
+        const int64_t pitch = g.ldc * (BF16OUT ? 2 : 4);
+#pragma unroll
+        for (int i = 0; i < TI; ++i)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+#pragma unroll
+                for (int j = 0; j < TJ; j += BF16OUT ? 2 : 1) {
+                    if constexpr (BF16OUT)
+                        *reinterpret_cast<bf2_t *>(p + j * 64) = bf2_t{(__bf16)acc[i][j][r], (__bf16)acc[i][j + 1][r]};
+                    else
+                        *reinterpret_cast<float *>(p + j * 128) = acc[i][j][r];
+                }
+                p += (r & 3) == 3 ? 5 * pitch : pitch;
+            }
+        return;
+    }
+    // edge tiles, accumulation, unaligned pairs: 32-row strips through LDS, one
+    // element per lane and store, in a rolled loop
+    constexpr int kPitch = 32 * TJ + 8;                         // floats; a wave's strip is 32 x (32 TJ)
+    static_assert(4 * 32 * kPitch * 4 <= RING * kStage, "the strips fit the ring");
+    __syncthreads();                                            // every wave has read its last stage
+    float *strip = reinterpret_cast<float *>(smem) + wave * 32 * kPitch;
+#pragma unroll
+    for (int i = 0; i < TI; ++i) {
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+#pragma unroll
+            for (int j = 0; j < TJ; ++j) {
+                const int col = BF16OUT ? 64 * (j >> 1) + 2 * (lane & 31) + (j & 1) : 32 * j + (lane & 31);
+                strip[(8 * (r >> 2) + 4 * half + (r & 3)) * kPitch + col] = acc[i][j][r];
+            }
+        __builtin_amdgcn_wave_barrier();
+        // 64 columns of a row per step, TJ / 2 steps a row
+        const int64_t left = g.M - (r0 + 32 * i);
+        const int rows = left < 32 ? (left < 0 ? 0 : (int)left) : 32;
+        for (int cc = lane; cc < 32 * TJ; cc += 64) {
+            if (c0 + cc >= g.N) continue;
+#pragma unroll 8
+            for (int rr = 0; rr < rows; ++rr) store_one<BF16OUT>(g, r0 + 32 * i + rr, c0 + cc, strip[rr * kPitch + cc]);
+        }
+        __builtin_amdgcn_wave_barrier();
+    }
+}
+
+// (32 TI) x (32 TJ) tiles, TI = TJ, K split over the four waves in whole units of 128.
+template <int FMT, int TI, int TJ, bool BF16OUT>
+__global__ __launch_bounds__(kThreads, 1) void gemm_ksplit_kernel(const GemmArgs g, uint32_t tiles_m, uint32_t tiles_n)
+{
+    constexpr int kWaves = kThreads / 64;
+    constexpr int kRows = 32 * (TI + TJ);
+    constexpr int CODES = kRows / 16, WORDS = (kRows + 63) / 64;        // loads per wave and stage
+    constexpr int kStage = kRows * 64 + WORDS * 256;            // per wave
+    constexpr bool PAIR = BF16OUT && TJ == 2;                   // interleaved output columns
+    constexpr int kRed = kWaves * TI * TJ * 4 * 64 * 16;        // partial tiles at the end
+    constexpr int kLds = kWaves * kRing * kStage > kRed ? kWaves * kRing * kStage : kRed;
+    __shared__ __attribute__((aligned(1024))) uint8_t smem[kLds];
+
+    uint32_t tm, tn;
+    tile_coords_of(blockIdx.x, tiles_m, tiles_n, 8u, tm, tn);
+    const int64_t m0 = (int64_t)tm * 32 * TI, n0 = (int64_t)tn * 32 * TJ;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int half = lane >> 5;
+
+    // this wave's stages [s0, s0 + n): units of 128 values over the active waves
+    // (an MXFP8 unit is two stages, so every wave starts on an even one)
+    const uint32_t units = (uint32_t)(g.K / 128), per_unit = 128 / Fmt<FMT>::kStepK;
+    const uint32_t active = units < (uint32_t)kWaves ? units : (uint32_t)kWaves;
+    const uint32_t u0 = (uint32_t)((uint64_t)units * wave / active), u1 = (uint32_t)((uint64_t)units * (wave + 1) / active);
+    const uint32_t s0 = u0 * per_unit, n = (uint32_t)wave < active ? (u1 - u0) * per_unit : 0;
+
+    // row t of the stage: A rows, then B rows
+    auto row_of = [&](int t, bool &is_a) __attribute__((always_inline)) -> int64_t {
+        is_a = t < 32 * TI;
+        const int tb = t - 32 * TI;
+        const int64_t r = is_a ? m0 + t : n0 + (PAIR ? interleaved_row(tb) : tb);
+        const int64_t lim = is_a ? g.M : g.N;
+        return r < lim ? r : lim - 1;
+    };
+    const uint8_t *pc[CODES], *pw[WORDS];
+    int64_t wstep[WORDS];                                       // bytes per stage (MXFP8: per two stages)
+#pragma unroll
+    for (int c = 0; c < CODES; ++c) {
+        const int t = 16 * c + (lane >> 2), c16 = ((lane & 3) ^ swz(t)) * 16;
+        bool is_a;
+        const int64_t r = row_of(t, is_a);
+        pc[c] = (is_a ? g.a + r * g.lda : g.b + r * g.ldb) + c16 + (uint64_t)s0 * 64;
+    }
+#pragma unroll
+    for (int c = 0; c < WORDS; ++c) {
+        int t = 64 * c + lane; t = t < kRows ? t : kRows - 1;
+        bool is_a;
+        const int64_t r = row_of(t, is_a);
+        const bool oned = is_a ? g.a1d : g.b1d;
+        const int64_t ld = is_a ? g.ldsa : g.ldsb;
+        wstep[c] = FMT != kFmtMxfp8 && oned ? ld : 4;
+        pw[c] = (is_a ? g.sa : g.sb) + word_row<FMT>(r, ld, oned) + (FMT == kFmtMxfp8 ? s0 >> 1 : s0) * wstep[c];
+    }
+    uint8_t *ring = smem + wave * (kRing * kStage);
+    const uint32_t lds0 = (uint32_t)(uintptr_t)ring;
+    auto load = [&](uint32_t s, bool words) __attribute__((always_inline)) {
+        const uint32_t stage = lds0 + (s % kRing) * kStage;
+#pragma unroll
+        for (int k = 0; k < CODES; ++k) lds_dma16(pc[k] + (uint64_t)s * 64, stage + k * 1024);
+        if (words) {
+#pragma unroll
+            for (int k = 0; k < WORDS; ++k)
+                lds_dma4(pw[k] + (FMT == kFmtMxfp8 ? s >> 1 : s) * wstep[k], stage + kRows * 64 + k * 256);
+        }
+    };
+
+    v16f acc[TI][TJ];
+#pragma unroll
+    for (int i = 0; i < TI; ++i)
+#pragma unroll
+        for (int j = 0; j < TJ; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
+
+    Frag fa0[TI], fb0[TJ], fa1[TI], fb1[TJ];
+    auto read = [&](auto word, uint32_t s, int k, Frag (&fa)[TI], Frag (&fb)[TJ]) __attribute__((always_inline)) {
+        const uint8_t *st = ring + (s % kRing) * kStage;
+        read_frag<decltype(word)::value>(k < TI ? fa[k] : fb[k - TI], st, st + kRows * 64, 32 * k + (lane & 31), half);
+    };
+    auto body = [&](auto par, uint32_t s, Frag (&fa)[TI], Frag (&fb)[TJ], Frag (&na)[TI], Frag (&nb)[TJ])
+                    __attribute__((always_inline)) {
+        constexpr int PAR = decltype(par)::value;
+        constexpr bool F8 = FMT == kFmtMxfp8;
+        wait_lgkm();                                    // stage s is in registers, its slot free
+        wait_next<FMT, PAR, CODES, WORDS>(n - 1 - s);
+        stage_products<FMT, PAR, TI, TJ, 1>(
+            acc, fa, fb, half,
+            [&](auto k) __attribute__((always_inline)) {
+                // past the last stage the slot's bytes are read and never used
+                if constexpr (F8 && PAR == 0) {         // an odd stage's words are the even one's
+                    read(std::false_type{}, s + 1, k, na, nb);
+                    if (k < TI) na[k < TI ? k : 0].w = fa[k < TI ? k : 0].w;
+                    else nb[k < TI ? 0 : k - TI].w = fb[k < TI ? 0 : k - TI].w;
+                } else {
+                    read(std::true_type{}, s + 1, k, na, nb);
+                }
+            },
+            [&](auto) __attribute__((always_inline)) { if (s + kRing < n) load(s + kRing, !F8 || PAR == 0); });
+    };
+
+    if (n > 0) {
+        for (uint32_t s = 0; s < kRing && s < n; ++s) load(s, FMT != kFmtMxfp8 || (s & 1) == 0);
+        wait_first<FMT, CODES, WORDS>(n);
+#pragma unroll
+        for (int k = 0; k < TI + TJ; ++k) read(std::true_type{}, 0, k, fa0, fb0);
+        uint32_t s = 0;
+        for (; s + 1 < n; s += 2) {
+            body(std::integral_constant<int, 0>{}, s, fa0, fb0, fa1, fb1);
+            body(std::integral_constant<int, 1>{}, s + 1, fa1, fb1, fa0, fb0);
+        }
+        if (FMT == kFmtFp4Block2D && s < n) body(std::integral_constant<int, 0>{}, s, fa0, fb0, fa1, fb1);
+    }
+
+    // partial tiles to LDS (the rings are drained): four accumulators of a lane
+    // as one 16-byte piece, pieces of a quad (i, q, j) lane by lane
+    __syncthreads();
+    uint4 *red = reinterpret_cast<uint4 *>(smem);
+    if (n > 0) {
+#pragma unroll
+        for (int i = 0; i < TI; ++i)
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+#pragma unroll
+                for (int j = 0; j < TJ; ++j)
+                    red[((wave * TI * 4 + i * 4 + q) * TJ + j) * 64 + lane] =
+                        make_uint4(f_bits(acc[i][j][4 * q]), f_bits(acc[i][j][4 * q + 1]), f_bits(acc[i][j][4 * q + 2]),
+                                   f_bits(acc[i][j][4 * q + 3]));
+    }
+    __syncthreads();
+    // wave q sums and writes row quads q of every 32-row strip: a lane has four
+    // consecutive rows of a column (PAIR: of two neighbouring ones)
+    const bool pairs = PAIR && n0 + 64 <= g.N && !g.accumulate && pair_stores(g);
+    const int q = wave;
+#pragma unroll
+    for (int i = 0; i < TI; ++i) {
+        float v[TJ][4];
+#pragma unroll
+        for (int j = 0; j < TJ; ++j) {
+#pragma unroll
+            for (int r = 0; r < 4; ++r) v[j][r] = 0.0f;
+            for (uint32_t w = 0; w < active; ++w) {
+                const uint4 p = red[((w * TI * 4 + i * 4 + q) * TJ + j) * 64 + lane];
+                v[j][0] += bits_f(p.x); v[j][1] += bits_f(p.y); v[j][2] += bits_f(p.z); v[j][3] += bits_f(p.w);
+            }
+        }
+        const int64_t row = m0 + i * 32 + 8 * q + 4 * half;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            if (row + r >= g.M) continue;
+            if (PAIR && pairs) {
+                *reinterpret_cast<bf2_t *>(reinterpret_cast<__bf16 *>(g.c) + (row + r) * g.ldc + n0 + 2 * (lane & 31)) =
+                    bf2_t{(__bf16)v[0][r], (__bf16)v[TJ - 1][r]};
+            } else {
+#pragma unroll
+                for (int j = 0; j < TJ; ++j) {
+                    const int64_t col = n0 + (PAIR ? 2 * (lane & 31) + j : 32 * j + (lane & 31));
+                    if (col < g.N) store_one<BF16OUT>(g, row + r, col, v[j][r]);
+                }
+            }
+        }
+    }
+}
+
+template <int FMT, int TI, int TJ, int RING, bool BF>
+hipError_t launch_tile(const GemmArgs &g, hipStream_t s)
+{
+    const int64_t tm = (g.M + 64 * TI - 1) / (64 * TI), tn = (g.N + 64 * TJ - 1) / (64 * TJ);
+    const dim3 grid((unsigned)(tm * tn)), block(kThreads);
+    if (FMT == kFmtMxfp8 || g.a1d || g.b1d)
+        hipLaunchKernelGGL((gemm_tile_kernel<FMT, TI, TJ, RING, 1, BF>), grid, block, 0, s, g, (uint32_t)tm, (uint32_t)tn);
+    else if constexpr (FMT != kFmtMxfp8)
+        hipLaunchKernelGGL((gemm_tile_kernel<FMT, TI, TJ, RING, 0, BF>), grid, block, 0, s, g, (uint32_t)tm, (uint32_t)tn);
+    return hipGetLastError();
+}
+
+template <int FMT, int TI, int TJ, bool BF>
+hipError_t launch_ksplit(const GemmArgs &g, hipStream_t s)
+{
+    const int64_t tm = (g.M + 32 * TI - 1) / (32 * TI), tn = (g.N + 32 * TJ - 1) / (32 * TJ);
+    hipLaunchKernelGGL((gemm_ksplit_kernel<FMT, TI, TJ, BF>), dim3((unsigned)(tm * tn)), dim3(kThreads), 0, s, g,
+                       (uint32_t)tm, (uint32_t)tn);
+    return hipGetLastError();
+}
+
+template <int FMT, bool BF>
+hipError_t launch_t(const GemmArgs &g, SmallTile tile, hipStream_t s)
+{
+    switch (tile) {
+    case kTile32: return launch_ksplit<FMT, 1, 1, BF>(g, s);
+    case kTile64: return launch_ksplit<FMT, 2, 2, BF>(g, s);
+    case kTile128: return launch_tile<FMT, 2, 2, 3, BF>(g, s);
+    default: return launch_tile<FMT, 4, 2, 3, BF>(g, s);
+    }
+}
+
+}  // namespace
+
+// The tile with the smallest modelled time: rounds of workgroups over the chip
+// (the 32 x 32 kernel holds two a CU, the others one), each a fixed part (address
+// setup, first loads, epilogue) plus a part per 128 values of K; the 256 x 256
+// kernels pay some of the fixed part once.  Microseconds fitted to timings on one
+// MI355X with a launch's own 2.5 us taken off (FP4, bf16 output).  Measured with
+// tiles of 32 / 64 / 128 / 256 x 128 / 256: 600 x 700 x 128 3.1 / 4.5 / 5.7 / 8.7 /
+// 12.2 us; 128 x 4096 x 4096 7.8 / 9.2 / 11.0 / 19.6 / 30.4; 512 x 4096 x 4096 21.0 /
+// 18.6 / 12.1 / 16.5 / 26.7; 2048 x 4096 x 4096 72 / 65 / 25.4 / 22.9 / 27.6; 777 x
+// 11008 x 4096 76 / 72 / 34 / 34 / 29; 4096 x 4096 x 4096 139 / 125 / 51 / 45 / 37.
+// `large`: the 256 x 256 kernels can take the problem.
+SmallTile pick_tile(const GemmArgs &g, int fmt, bool large)
+{
+    struct Cost { int32_t tm, tn, per_cu; float once, round, unit[2]; };      // unit: FP4, MXFP8
+    static const Cost cost[] = {{32, 32, 2, 0.0f, 1.0f, {0.14f, 0.22f}},
+                                {64, 64, 1, 0.0f, 2.0f, {0.21f, 0.375f}},
+                                {128, 128, 1, 0.0f, 3.0f, {0.29f, 0.55f}},
+                                {256, 128, 1, 0.0f, 5.5f, {0.47f, 0.90f}},
+                                {256, 256, 1, 4.0f, 5.0f, {0.82f, 1.55f}}};
+    const int64_t cus = cu_count(), units = g.K / 128;
+    const int top = large ? kTile256 : kTile256x128;
+    int best = top;
+    float least = 0.0f;
+    for (int k = top; k >= 0; --k) {
+        const Cost &c = cost[k];
+        const int64_t tiles = ((g.M + c.tm - 1) / c.tm) * ((g.N + c.tn - 1) / c.tn), slots = cus * c.per_cu;
+        const float t = c.once + (float)((tiles + slots - 1) / slots) * (c.round + (float)units * c.unit[fmt == kFmtMxfp8]);
+        if (k == top || t < least) { best = k; least = t; }
+    }
+    return (SmallTile)best;
+}
+
+hipError_t launch_gemm_small(const GemmArgs &g, int fmt, int c_is_bf16, SmallTile tile, hipStream_t stream)
+{
+    if (fmt == kFmtFp4Block2D)
+        return c_is_bf16 ? launch_t<kFmtFp4Block2D, true>(g, tile, stream) : launch_t<kFmtFp4Block2D, false>(g, tile, stream);
+    return c_is_bf16 ? launch_t<kFmtMxfp8, true>(g, tile, stream) : launch_t<kFmtMxfp8, false>(g, tile, stream);
+}
+
+}  // namespace q2d

@@ -69,6 +69,13 @@ hipError_t launch_gemm_quantized(const GemmArgs &g, hipStream_t stream);
 
 hipError_t launch_gemm(const GemmArgs &g, int fmt, int c_is_bf16, hipStream_t stream);
 
+// Output tiles of the dense GEMMs, by size: the small-tile kernels, which take any
+// problem, and the 256 x 256 kernels.
+enum SmallTile { kTile32 = 0, kTile64 = 1, kTile128 = 2, kTile256x128 = 3, kTile256 = 4 };
+
+SmallTile pick_tile(const GemmArgs &g, int fmt, bool large);
+hipError_t launch_gemm_small(const GemmArgs &g, int fmt, int c_is_bf16, SmallTile tile, hipStream_t stream);
+
 // Grouped (MoE) GEMMs over nseg experts with device segment offsets.
 //   ragged M: A = grouped rows (padded), op(B) of expert e is rows
 //             [e*N, (e+1)*N) (b_group_rows = N) or K columns [e*K, (e+1)*K)
