@@ -216,7 +216,7 @@ def kind_of(kernel_name: str):
         return "gemm_fp4" if m.group(1) == "0" else "gemm_fp8"
     m = re.search(r"fp4_quantize_kernel<([^>]*)>", kernel_name)
     if m:
-        # template arguments: element type, VEC, SR, ALIGNED8, GROUPED, column waves, 1D
+        # template arguments: element type, VEC, SR, row waves, GROUPED, column waves, 1D
         a = [t.strip() for t in m.group(1).split(",")]
         if a[6] == "true":
             return "quant_fp4_1d"

@@ -3,6 +3,8 @@
 
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+#include <type_traits>
+#include <utility>
 
 namespace q2d {
 
@@ -10,6 +12,37 @@ typedef int v4i __attribute__((ext_vector_type(4)));
 typedef int v8i __attribute__((ext_vector_type(8)));
 typedef float v4f __attribute__((ext_vector_type(4)));
 typedef float v16f __attribute__((ext_vector_type(16)));
+
+typedef unsigned int u4v __attribute__((ext_vector_type(4)));
+
+// 16-byte streaming load: a quantizer's input is read once, so it should not
+// displace cache lines that are reused
+__device__ __forceinline__ uint4 load_stream16(const uint8_t *p)
+{
+    const u4v v = __builtin_nontemporal_load(reinterpret_cast<const u4v *>(p));
+    return make_uint4(v.x, v.y, v.z, v.w);
+}
+
+// 16-byte load from an address aligned to 4 bytes only; cached, since neighbouring
+// loads meet in one line
+typedef u4v u4v_a4 __attribute__((aligned(4)));
+__device__ __forceinline__ uint4 load_words16(const uint8_t *p)
+{
+    const u4v v = *reinterpret_cast<const u4v_a4 *>(p);
+    return make_uint4(v.x, v.y, v.z, v.w);
+}
+
+// f(std::integral_constant<int, 0>) ... f(std::integral_constant<int, N - 1>), in order
+template <typename F, int... Is>
+__device__ __forceinline__ void unroll_seq(F &&f, std::integer_sequence<int, Is...>)
+{
+    (f(std::integral_constant<int, Is>{}), ...);
+}
+template <int N, typename F>
+__device__ __forceinline__ void unroll(F &&f)
+{
+    unroll_seq(f, std::make_integer_sequence<int, N>{});
+}
 
 __device__ __forceinline__ float bits_f(uint32_t u) { return __uint_as_float(u); }
 __device__ __forceinline__ uint32_t f_bits(float f) { return __float_as_uint(f); }
@@ -110,6 +143,89 @@ __device__ __forceinline__ uint16_t f_to_bf16_rne(float f)
     if ((b & 0x7F800000u) == 0x7F800000u) return (uint16_t)((b >> 16) | ((b & 0xFFFFu) ? 0x40u : 0u));
     b += 0x7FFFu + ((b >> 16) & 1u);
     return (uint16_t)(b >> 16);
+}
+
+// A lane's 8 x 8 sub-block of a matrix with contiguous rows of `pitch` bytes, from
+// address p, as 32-bit words (E = 2: bf16 pairs, v[i][k] holds columns 2k and
+// 2k + 1 of row i; E = 4: float32).  rows, cols: what the matrix has from p on (at
+// most 0: nothing); words outside it are 0.
+//
+// ALIGNED: p and the pitch are multiples of 16 bytes.  Otherwise loads of aligned
+// 4-byte words, and a matrix of at least 8 columns.
+//
+// No load is skipped, so that all are in flight together: past the edge they go to
+// the matrix's last row and its last 16-byte piece (ALIGNED: the one that holds the
+// last column) or last 8 columns, and the words are put in place afterwards.
+template <int E, bool ALIGNED, int NV>
+__device__ __forceinline__ void load_sub_block(uint32_t (&v)[8][NV], const uint8_t *p, int64_t pitch, int64_t rows,
+                                               int64_t cols)
+{
+    static_assert(NV == 2 * E, "8 elements");
+    constexpr int NB = E / 2;                   // 16-byte pieces of a row
+    const bool edge = __builtin_amdgcn_ballot_w64(rows < 8 || cols < 8) != 0;
+    const uint8_t *q = p;
+    if (edge && !ALIGNED && cols < 8) q += (cols - 8) * E;
+    const int64_t last = (cols * E - 1) & ~int64_t(15);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        const uint8_t *r = q + (!edge || i < rows ? (int64_t)i * pitch : (rows - 1) * pitch);
+#pragma unroll
+        for (int t = 0; t < NB; ++t) {
+            uint4 x;
+            if constexpr (ALIGNED) {
+                x = load_stream16(r + (!edge || 16 * t <= last ? 16 * t : last));
+            } else if constexpr (E == 4) {
+                x = load_words16(r + 16 * t);
+            } else {
+                // the words that hold the eight bf16 values: four from the word of the
+                // first one on and, if that is its upper half, the one behind them
+                // (16-byte loads at 2-byte addresses run at less than half the rate)
+                const bool odd = (reinterpret_cast<uintptr_t>(r) & 2) != 0;
+                const uint8_t *rw = odd ? r - 2 : r;
+                const uint4 y = load_words16(rw);
+                const uint32_t z = *reinterpret_cast<const uint32_t *>(odd ? rw + 16 : rw + 12);
+                x = odd ? make_uint4((y.x >> 16) | (y.y << 16), (y.y >> 16) | (y.z << 16), (y.z >> 16) | (y.w << 16),
+                                     (y.w >> 16) | (z << 16))
+                        : y;
+            }
+            v[i][4 * t] = x.x; v[i][4 * t + 1] = x.y; v[i][4 * t + 2] = x.z; v[i][4 * t + 3] = x.w;
+        }
+    }
+    if (!edge) return;
+    const int nr = rows < 8 ? (int)(rows < 0 ? 0 : rows) : 8, nc = cols < 8 ? (int)(cols < 0 ? 0 : cols) : 8;
+    if (!ALIGNED) {
+        // the lane that holds the last columns read 8 - nc earlier ones before them
+        const int s = (8 - nc) & 7;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            if (E == 4) {
+#pragma unroll
+                for (int k = 0; k < NV; ++k) v[i][k] = (s & 4) && k + 4 < NV ? v[i][k + 4 < NV ? k + 4 : k] : v[i][k];
+            }
+            constexpr int S2 = E == 4 ? 2 : 1, S4 = 2;
+            if (E == 2) {
+#pragma unroll
+                for (int k = 0; k + S4 < NV; ++k) v[i][k] = (s & 4) ? v[i][k + S4] : v[i][k];
+            }
+#pragma unroll
+            for (int k = 0; k + S2 < NV; ++k) v[i][k] = (s & 2) ? v[i][k + S2] : v[i][k];
+            if (E == 4) {
+#pragma unroll
+                for (int k = 0; k + 1 < NV; ++k) v[i][k] = (s & 1) ? v[i][k + 1] : v[i][k];
+            } else {
+#pragma unroll
+                for (int k = 0; k < NV; ++k)
+                    v[i][k] = (s & 1) ? (v[i][k] >> 16) | (k + 1 < NV ? v[i][k + 1 < NV ? k + 1 : k] << 16 : 0u) : v[i][k];
+            }
+        }
+    }
+#pragma unroll
+    for (int k = 0; k < NV; ++k) {
+        const uint32_t keep = E == 4 ? (k < nc ? ~0u : 0u)
+                                     : (2 * k < nc ? 0xFFFFu : 0u) | (2 * k + 1 < nc ? 0xFFFF0000u : 0u);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) v[i][k] = i < nr ? v[i][k] & keep : 0u;
+    }
 }
 
 // ---- grouped (MoE) segment tables, built per workgroup in LDS

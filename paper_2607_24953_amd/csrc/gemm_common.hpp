@@ -116,17 +116,5 @@ __device__ __forceinline__ int interleaved_row(int t)
     return (t & ~127) + 64 * (j >> 1) + 2 * l + (j & 1);
 }
 
-// f(std::integral_constant<int, 0>) ... f(std::integral_constant<int, N - 1>), in order
-template <typename F, int... Is>
-__device__ __forceinline__ void unroll_seq(F &&f, std::integer_sequence<int, Is...>)
-{
-    (f(std::integral_constant<int, Is>{}), ...);
-}
-template <int N, typename F>
-__device__ __forceinline__ void unroll(F &&f)
-{
-    unroll_seq(f, std::make_integer_sequence<int, N>{});
-}
-
 }  // namespace
 }  // namespace q2d

@@ -4,8 +4,8 @@
 // nearest or Philox stochastic rounding, and both packed layouts (row-packed
 // codes and column-packed codes_t) plus the scale grid and its transpose.
 //
-// Work split: a workgroup owns a 128-row tile of WC x 128 columns; each wave
-// owns a 32 x 128 strip (four 32 x 32 blocks side by side).  Lane l owns an
+// Work split: a workgroup owns a 128-row tile of WC x 128 columns (small inputs:
+// a strip of its own); each wave owns a 32 x 128 strip (four 32 x 32 blocks side by side).  Lane l owns an
 // 8 x 8 sub-block: rows 8*(l/16) .. +7 and columns 8*(l%16) .. +7 of the strip.
 // A row of the sub-block is one 16-byte load (bf16), so every load
 // instruction of the wave reads four 256-byte row segments.  The 8 x 8
@@ -48,20 +48,8 @@ namespace q2d {
 
 namespace {
 
-constexpr int kTile = 128;          // tile rows
-
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef float f2v __attribute__((ext_vector_type(2)));
-typedef unsigned int u4v __attribute__((ext_vector_type(4)));
-
-// 16-byte streaming load: the input is read once, so it should not displace
-// cache lines that are reused
-__device__ __forceinline__ uint4 load_stream16(const void *p)
-{
-    const u4v v = __builtin_nontemporal_load(reinterpret_cast<const u4v *>(p));
-    return make_uint4(v.x, v.y, v.z, v.w);
-}
-
 typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
 
 template <typename T>
@@ -145,36 +133,46 @@ __device__ __forceinline__ void nibble_transpose8(const uint32_t in[8], uint32_t
     }
 }
 
-// Philox4x32-10 block with one 32x32->64 multiply per product (v_mad_u64_u32)
-// and one three-input xor per output word.
-__device__ __forceinline__ void philox_block(uint64_t g, uint32_t o0, uint32_t o1, uint32_t k0, uint32_t k1,
+// Philox4x32-10 block of counter (g, 0, o0, o1), one 32x32->64 multiply per product
+// (v_mad_u64_u32) and one three-input xor per output word.  The offset and the
+// upper counter word are the same for every lane, so one product of each of the
+// first two rounds is scalar: 18 vector products instead of 20.
+__device__ __forceinline__ void philox_block(uint32_t g, uint32_t o0, uint32_t o1, uint32_t k0, uint32_t k1,
                                              uint32_t w[4])
 {
-    uint32_t c0 = (uint32_t)g, c1 = (uint32_t)(g >> 32), c2 = o0, c3 = o1;
+    const uint64_t s0 = (uint64_t)0xCD9E8D57u * o0, p0 = (uint64_t)0xD2511F53u * g;
+    const uint32_t u0 = (uint32_t)(s0 >> 32) ^ k0, u1 = (uint32_t)s0;                 // round 0: words 0 and 1
+    const uint32_t v2 = (uint32_t)(p0 >> 32) ^ (o1 ^ k1), v3 = (uint32_t)p0;          // words 2 and 3
+    k0 += 0x9E3779B9u; k1 += 0xBB67AE85u;
+    const uint64_t s1 = (uint64_t)0xD2511F53u * u0, p1 = (uint64_t)0xCD9E8D57u * v2;
+    uint32_t c0 = (uint32_t)(p1 >> 32) ^ (u1 ^ k0), c1 = (uint32_t)p1;                // round 1
+    uint32_t c2 = v3 ^ ((uint32_t)(s1 >> 32) ^ k1), c3 = (uint32_t)s1;
 #pragma unroll
-    for (int r = 0; r < 10; ++r) {
-        if (r) { k0 += 0x9E3779B9u; k1 += 0xBB67AE85u; }
-        const uint64_t p0 = (uint64_t)0xD2511F53u * c0;
-        const uint64_t p1 = (uint64_t)0xCD9E8D57u * c2;
-        const uint32_t n0 = xor3_uniform((uint32_t)(p1 >> 32), c1, k0);
-        const uint32_t n2 = xor3_uniform((uint32_t)(p0 >> 32), c3, k1);
-        c0 = n0; c1 = (uint32_t)p1; c2 = n2; c3 = (uint32_t)p0;
+    for (int r = 2; r < 10; ++r) {
+        k0 += 0x9E3779B9u; k1 += 0xBB67AE85u;
+        const uint64_t q0 = (uint64_t)0xD2511F53u * c0;
+        const uint64_t q1 = (uint64_t)0xCD9E8D57u * c2;
+        const uint32_t n0 = xor3_uniform((uint32_t)(q1 >> 32), c1, k0);
+        const uint32_t n2 = r == 2 ? (uint32_t)(q0 >> 32) ^ (c3 ^ k1) : xor3_uniform((uint32_t)(q0 >> 32), c3, k1);
+        c0 = n0; c1 = (uint32_t)q1; c2 = n2; c3 = (uint32_t)q0;
     }
     w[0] = c0; w[1] = c1; w[2] = c2; w[3] = c3;
 }
 
 // One 128-row tile (row tile tr, column tile tc) of the quantization described
 // by `a` (for a grouped tensor, `a` is already narrowed to the tile's segment).
-// VEC: rows are read as aligned 8-element vectors (stride_c == 1).
-// SR: stochastic rounding.  ALIGNED8: every sub-block row starts at a storage
-// index that is a multiple of 8, so one Philox block serves its 8 elements.
-// GROUPED: the rows are expert segments (see QuantArgs).  WC: 128-column
-// strips per tile (waves side by side).  ONED: 1 x 32 / 32 x 1 blocks.
-template <typename T, bool VEC, bool SR, bool ALIGNED8, bool GROUPED, int WC, bool ONED>
+// VEC: 0 -- element by element; 1 -- contiguous rows (stride_c == 1) of any pitch and
+// alignment, read as 16-byte windows; 2 -- rows on 16-byte boundaries (with SR, also
+// on storage indices that are multiples of 8).  1 and 2 with SR: every storage
+// index is below 2^35, so the upper Philox counter word is 0.
+// SR: stochastic rounding.
+// GROUPED: the rows are expert segments (see QuantArgs).  WR x WC:
+// 32 x 128 strips per tile, one a wave.  ONED: 1 x 32 / 32 x 1 blocks.
+template <typename T, int VEC, bool SR, int WR, bool GROUPED, int WC, bool ONED>
 __device__ __forceinline__ void quantize_tile(QuantArgs a, const int64_t tr, const int64_t tc)
 {
-    constexpr int kTC = 128 * WC;
-    constexpr int kThreads = 256 * WC;
+    constexpr int kTC = 128 * WC, kTile = 32 * WR;
+    constexpr int kThreads = 64 * WR * WC;
     constexpr bool PK = sizeof(T) == 2;     // bf16: two elements per register
     constexpr int NV = PK ? 4 : 8;
     const int lane = threadIdx.x & 63;
@@ -189,51 +187,18 @@ __device__ __forceinline__ void quantize_tile(QuantArgs a, const int64_t tr, con
     // ---- load the 8 x 8 sub-block (0 outside R x C).  bf16: v[i][k] holds
     // columns 2k (low half) and 2k+1 (high half) of row i; fp32: bit patterns.
     uint32_t v[8][NV];
-    if (PK) {
-        if (VEC && c0 + 8 <= a.cols) {
-            const T *xr = x + r0 * a.stride_r + c0;
-#pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                uint4 q = make_uint4(0u, 0u, 0u, 0u);
-                if (r0 + i < a.rows) q = load_stream16(xr);
-                v[i][0] = q.x; v[i][1] = q.y; v[i][2] = q.z; v[i][3] = q.w;
-                xr += a.stride_r;
-            }
-        } else {
-#pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                const int64_t r = r0 + i;
-#pragma unroll
-                for (int k = 0; k < NV; ++k) {
-                    const int64_t c = c0 + 2 * k;
-                    const uint32_t lo = (r < a.rows && c < a.cols) ? Elem<T>::bits(x + r * a.stride_r + c * a.stride_c) : 0u;
-                    const uint32_t hi = (r < a.rows && c + 1 < a.cols) ? Elem<T>::bits(x + r * a.stride_r + (c + 1) * a.stride_c) : 0u;
-                    v[i][k] = (lo >> 16) | hi;
-                }
-            }
-        }
-    } else if (VEC && c0 + 8 <= a.cols) {
-        const T *xr = x + r0 * a.stride_r + c0;
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            uint4 q0 = make_uint4(0u, 0u, 0u, 0u), q1 = q0;
-            if (r0 + i < a.rows) {
-                q0 = load_stream16(xr);
-                q1 = load_stream16(xr + 4);
-            }
-            v[i][0] = q0.x; v[i][1] = q0.y; v[i][2] = q0.z; v[i][3] = q0.w;
-            v[i][NV - 4] = q1.x; v[i][NV - 3] = q1.y; v[i][NV - 2] = q1.z; v[i][NV - 1] = q1.w;
-            xr += a.stride_r;
-        }
+    if constexpr (VEC != 0) {
+        load_sub_block<(int)sizeof(T), VEC == 2>(v, reinterpret_cast<const uint8_t *>(x + r0 * a.stride_r + c0),
+                                                 a.stride_r * (int64_t)sizeof(T), a.rows - r0, a.cols - c0);
     } else {
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
             const int64_t r = r0 + i;
+            auto at = [&](int64_t c) __attribute__((always_inline)) -> uint32_t {
+                return r < a.rows && c < a.cols ? Elem<T>::bits(x + r * a.stride_r + c * a.stride_c) : 0u;
+            };
 #pragma unroll
-            for (int j = 0; j < NV; ++j) {
-                const int64_t c = c0 + j;
-                v[i][j] = (r < a.rows && c < a.cols) ? Elem<T>::bits(x + r * a.stride_r + c * a.stride_c) : 0u;
-            }
+            for (int k = 0; k < NV; ++k) v[i][k] = PK ? (at(c0 + 2 * k) >> 16) | at(c0 + 2 * k + 1) : at(c0 + k);
         }
     }
     // float32 bit pattern of element (i, j)
@@ -296,10 +261,10 @@ __device__ __forceinline__ void quantize_tile(QuantArgs a, const int64_t tr, con
             cm[j] = max(cm[j], (uint32_t)__shfl_xor((int)cm[j], 32));
         }
     }
-    if (!ONED && !GROUPED && a.block == 64) {
+    if (WR > 1 && !ONED && !GROUPED && a.block == 64) {
         // 64 x 64 blocks: the 32 x 32 block beside it in this wave (lane bit 2), then
         // the 32-row strip of the paired wave through LDS
-        __shared__ uint32_t am64[4][2 * WC];
+        __shared__ uint32_t am64[WR][2 * WC];
         am = max(am, (uint32_t)__shfl_xor((int)am, 4));
         if (rg == 0 && (cc & 7) == 0) am64[wr][wc * 2 + (cc >> 3)] = am;
         __syncthreads();
@@ -389,29 +354,45 @@ __device__ __forceinline__ void quantize_tile(QuantArgs a, const int64_t tr, con
     } else {
         const uint32_t k0 = (uint32_t)a.seed, k1 = (uint32_t)(a.seed >> 32);
         const uint32_t o0 = (uint32_t)a.offset, o1 = (uint32_t)(a.offset >> 32);
+        // Rows that start off a Philox block (VEC 1): a row's eight draws
+        // straddle two blocks, the second of which is the first of the lane to the
+        // right.  Only the strip's last lane of a row lacks a neighbour: lane i < 8 of
+        // the 16 lanes of a row group computes the block behind row i for it.
+        uint32_t xw[4] = {0, 0, 0, 0};
+        if (VEC == 1) {
+            const int64_t idx = a.index_base + (r0 + (cc & 7)) * a.stride_r + (c0 - 8 * cc) + 128;
+            philox_block((uint32_t)((uint64_t)idx >> 3), o0, o1, k0, k1, xw);
+        }
         // the draws of row i (storage index idx_row of its first element) as
         // seeds r16 << 16
-        auto row_draws = [&](int i, int64_t idx_row, uint32_t s16[8]) __attribute__((always_inline)) {
-            uint32_t w[4] = {0, 0, 0, 0}, w2[4] = {0, 0, 0, 0};
+        auto row_draws = [&](auto ic, int64_t idx_row, uint32_t s16[8]) __attribute__((always_inline)) {
+            constexpr int i = decltype(ic)::value;
+            uint32_t w[8] = {0, 0, 0, 0, 0, 0, 0, 0};
             if (VEC) {
-                philox_block((uint64_t)idx_row >> 3, o0, o1, k0, k1, w);
-                if (!ALIGNED8) philox_block(((uint64_t)idx_row >> 3) + 1, o0, o1, k0, k1, w2);
+                philox_block((uint32_t)((uint64_t)idx_row >> 3), o0, o1, k0, k1, w);
+                if constexpr (VEC == 1) {
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        // row_newbcast:i, then row_shl:1 (lane 15 keeps the first operand)
+                        const int edge = __builtin_amdgcn_update_dpp(0, (int)xw[j], 0x150 + i, 0xF, 0xF, false);
+                        w[4 + j] = (uint32_t)__builtin_amdgcn_update_dpp(edge, (int)w[j], 0x101, 0xF, 0xF, false);
+                    }
+                    // halves sh .. sh + 7 of the sixteen; sh is the same for every lane
+                    // (r0 and c0 are multiples of 8)
+                    const int sh = (int)((a.index_base + i * a.stride_r) & 7);
+#pragma unroll
+                    for (int j = 0; j < 6; ++j) w[j] = (sh & 4) ? w[j + 2] : w[j];
+#pragma unroll
+                    for (int j = 0; j < 5; ++j) w[j] = (sh & 2) ? w[j + 1] : w[j];
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) w[j] = (sh & 1) ? (w[j] >> 16) | (w[j + 1] << 16) : w[j];
+                }
             }
 #pragma unroll
             for (int j = 0; j < 8; ++j) {
                 uint32_t r;
                 if (VEC) {
-                    if (ALIGNED8) {
-                        r = (j & 1) ? (w[j >> 1] & 0xFFFF0000u) : (w[j >> 1] << 16);
-                    } else {
-                        // the row's eight draws straddle two Philox blocks
-                        const uint32_t q = (uint32_t)(idx_row & 7) + (uint32_t)j;     // 0..14
-                        const uint32_t sq = q & 7u;
-                        const uint32_t wa = (sq & 4u) ? ((sq & 2u) ? w[3] : w[2]) : ((sq & 2u) ? w[1] : w[0]);
-                        const uint32_t wb = (sq & 4u) ? ((sq & 2u) ? w2[3] : w2[2]) : ((sq & 2u) ? w2[1] : w2[0]);
-                        const uint32_t ww = q < 8u ? wa : wb;
-                        r = (sq & 1u) ? (ww & 0xFFFF0000u) : (ww << 16);
-                    }
+                    r = (j & 1) ? (w[j >> 1] & 0xFFFF0000u) : (w[j >> 1] << 16);
                 } else {
                     const uint64_t idx = (uint64_t)(a.index_base + (r0 + i) * a.stride_r + (c0 + j) * a.stride_c);
                     r = sr_draw(idx, k0, k1, o0, o1) << 16;
@@ -424,10 +405,10 @@ __device__ __forceinline__ void quantize_tile(QuantArgs a, const int64_t tr, con
             // 2D blocks: both layouts share the block scale, so every element is
             // converted once, row by row; the column-packed words are the 8 x 8
             // nibble transpose of the row-packed ones
-#pragma unroll
-            for (int i = 0; i < 8; ++i) {
+            unroll<8>([&](auto ic) __attribute__((always_inline)) {
+                constexpr int i = decltype(ic)::value;
                 uint32_t s16[8];
-                row_draws(i, idx0, s16);
+                row_draws(ic, idx0, s16);
                 idx0 += a.stride_r;
                 uint32_t w = 0;
 #pragma unroll
@@ -439,20 +420,19 @@ __device__ __forceinline__ void quantize_tile(QuantArgs a, const int64_t tr, con
                     w |= ((lo & 0x0F0F0F0Fu) | (hi & 0xF0F0F0F0u)) & (0xFFu << (8 * k));
                 }
                 rowp[i] = w;
-            }
+            });
             nibble_transpose8(rowp, colp);
         } else {
 #pragma unroll
             for (int i = 0; i < 8; ++i) { rowp[i] = 0; colp[i] = 0; }
-#pragma unroll
-            for (int m = 0; m < 4; ++m) {
+            unroll<4>([&](auto mc) __attribute__((always_inline)) {
+                constexpr int m = decltype(mc)::value;
                 // draws of rows 2m and 2m+1 as seeds r16 << 16
                 uint32_t s16[2][8];
-#pragma unroll
-                for (int h = 0; h < 2; ++h) {
-                    row_draws(2 * m + h, idx0, s16[h]);
+                unroll<2>([&](auto hc) __attribute__((always_inline)) {
+                    row_draws(std::integral_constant<int, 2 * m + decltype(hc)::value>{}, idx0, s16[decltype(hc)::value]);
                     idx0 += a.stride_r;
-                }
+                });
                 // rows 2m and 2m+1: pairs (2k, 2k+1) into byte k
 #pragma unroll
                 for (int h = 0; h < 2; ++h) {
@@ -477,7 +457,7 @@ __device__ __forceinline__ void quantize_tile(QuantArgs a, const int64_t tr, con
                     const uint32_t hi = sr_pair(m, pr, s16[1][j] >> 1, sc);
                     colp[j] |= (lo & (0x0Fu << (8 * m))) | (hi & (0xF0u << (8 * m)));
                 }
-            }
+            });
         }
     }
     if (!ONED && !finite) {
@@ -495,9 +475,9 @@ __device__ __forceinline__ void quantize_tile(QuantArgs a, const int64_t tr, con
     // ---- stores through LDS: 16 bytes per lane, codes rows r < store_rows as
     // WC * 64-byte runs, codes_t rows c < C as 64-byte runs
     __shared__ uint32_t st_r[kTile][16 * WC + 1];
-    __shared__ uint32_t st_c[kTC][17];
+    __shared__ uint32_t st_c[kTC][4 * WR + 1];
     __shared__ uint8_t st_rs[ONED ? kTile : 1][4 * WC];     // 1D: row scales of the tile
-    __shared__ uint8_t st_cs[ONED ? kTC : 1][4];            // 1D: column scales of the tile
+    __shared__ uint8_t st_cs[ONED ? kTC : 1][WR];            // 1D: column scales of the tile
     {
         // the lane geometry again, from the thread index: cheaper than keeping it
         // live across the conversion (the opaque copy stops the compiler from
@@ -538,7 +518,7 @@ __device__ __forceinline__ void quantize_tile(QuantArgs a, const int64_t tr, con
             }
         }
         if (a.codes_t) {
-            const int line = item >> 2, part = item & 3;
+            const int line = item / WR, part = item % WR;
             const int64_t c = tc * kTC + line;
             if (c < a.cols) {
                 const uint4 w = make_uint4(st_c[line][4 * part], st_c[line][4 * part + 1],
@@ -583,19 +563,19 @@ __device__ __forceinline__ void quantize_tile(QuantArgs a, const int64_t tr, con
 }
 
 // A lane holds its 8 x 8 sub-block (32 registers of bf16 pairs, 64 of float32)
-// and converts each element once, so the bf16 vector-load variants take 91-115
-// VGPRs with nothing spilled (four or five waves per SIMD).  Of the bounds below
-// (at most 168 VGPRs for stochastic rounding, whose Philox latency needs three
-// waves per SIMD; at most 128 for round to nearest) only the float32
-// round-to-nearest variants reach theirs.
+// and converts each element once, so the aligned bf16 variants take 43-50 VGPRs
+// (grouped 67-75) with nothing spilled.  Of the bounds below (at most 168 VGPRs for
+// stochastic rounding, whose Philox latency needs three waves per SIMD; at most 128
+// for round to nearest) only the float32 round-to-nearest variants reach theirs.
 // Spilled registers cost HBM writes here, not only latency: every wave's spill
 // lines end up evicted by the streaming traffic.
-template <typename T, bool VEC, bool SR, bool ALIGNED8, bool GROUPED, int WC, bool ONED>
-__global__ __launch_bounds__(256 * WC)
-__attribute__((amdgpu_waves_per_eu(VEC && SR ? 3 : (VEC ? 4 : 1)))) void fp4_quantize_kernel(QuantArgs a)
+template <typename T, int VEC, bool SR, int WR, bool GROUPED, int WC, bool ONED>
+__global__ __launch_bounds__(64 * WR * WC)
+__attribute__((amdgpu_waves_per_eu(VEC && SR ? (ONED && VEC == 1 ? 2 : 3) : (VEC ? 4 : 1)))) void fp4_quantize_kernel(QuantArgs a)
 {
     static_assert(!(ONED && GROUPED), "grouped tensors use 2D blocks");
-    constexpr int kTC = 128 * WC;
+    static_assert(WR == 4 || (WR == 1 && !ONED && !GROUPED), "a strip of its own: dense 2D blocks of 32");
+    constexpr int kTC = 128 * WC, kTile = 32 * WR;
     const int64_t tiles_c = (a.cols_pad + kTC - 1) / kTC;
     if constexpr (GROUPED) {
         // padded start rows of the segments, built once per workgroup; the
@@ -628,60 +608,88 @@ __attribute__((amdgpu_waves_per_eu(VEC && SR ? 3 : (VEC ? 4 : 1)))) void fp4_qua
             if (b.codes_t) b.codes_t += p_e / 2;
             if (b.scales) b.scales += (int64_t)(p_e / 32) * a.ld_scales;
             if (b.scales_t) b.scales_t += p_e / 32;
-            quantize_tile<T, VEC, SR, ALIGNED8, GROUPED, WC, ONED>(b, (prow - p_e) / kTile, tc);
+            quantize_tile<T, VEC, SR, WR, GROUPED, WC, ONED>(b, (prow - p_e) / kTile, tc);
             __syncthreads();                // the tile's LDS staging is reused by the next
         }
     } else {
         const int64_t tile = blockIdx.x;
         const int64_t tr = tile / tiles_c;
-        quantize_tile<T, VEC, SR, ALIGNED8, GROUPED, WC, ONED>(a, tr, tile - tr * tiles_c);
+        quantize_tile<T, VEC, SR, WR, GROUPED, WC, ONED>(a, tr, tile - tr * tiles_c);
     }
 }
 
-template <typename T, bool VEC, bool SR, bool A8, bool G, bool ONED>
-hipError_t launch_t(const QuantArgs &a, hipStream_t s)
+template <typename T, int VEC, bool SR, bool G, int WR, int WC, bool ONED>
+hipError_t launch_w(const QuantArgs &a, hipStream_t s)
 {
-    // 256-column tiles of 8 waves in both rounding modes: the row-packed codes
-    // leave as whole 128-byte lines
-    constexpr int WC = 2;
-    int64_t nb = (a.rows_pad / kTile) * ((a.cols_pad + 128 * WC - 1) / (128 * WC));
+    int64_t nb = (a.rows_pad / (32 * WR)) * ((a.cols_pad + 128 * WC - 1) / (128 * WC));
     // grouped: each workgroup walks several tiles, so that the segment table is
     // built once per few tiles (the bound covers every padded segment's tiles);
     // 8 per CU keeps the last round of tiles short
     if (G) nb = nb < 8 * (int64_t)cu_count() ? nb : 8 * (int64_t)cu_count();
-    hipLaunchKernelGGL((fp4_quantize_kernel<T, VEC, SR, A8, G, WC, ONED>), dim3((unsigned)nb), dim3(256 * WC), 0, s,
+    // an input larger than the 256 MB Infinity Cache streams from HBM, and two
+    // workgroups (16 waves) a CU read it faster than the three or four that fit: 128.6
+    // against 134 us for 16384 x 12288 bf16, round to nearest (129.4 against 138,
+    // stochastic); below that size more waves hide more latency (8192 x 5632 SR: 31.5
+    // against 33.8 us).  Unused dynamic LDS holds the others off.
+    constexpr int kStatic = G ? 42516 : 34368;
+    const bool streams = WR == 4 && a.rows * a.cols * (int64_t)sizeof(T) > (int64_t(256) << 20);
+    const unsigned lds = streams ? (unsigned)(80000 - kStatic) : 0;
+    hipLaunchKernelGGL((fp4_quantize_kernel<T, VEC, SR, WR, G, WC, ONED>), dim3((unsigned)nb), dim3(64 * WR * WC), lds, s,
                        a);
     return hipGetLastError();
 }
 
-template <typename T, bool G, bool ONED>
-hipError_t launch_dtype(const QuantArgs &a, bool vec, bool sr, bool a8, hipStream_t s)
+constexpr int64_t kStripTiles = 128;
+
+template <typename T, int VEC, bool SR, bool G, bool ONED>
+hipError_t launch_t(const QuantArgs &a, hipStream_t s)
 {
-    if (vec) {
-        if (!sr) return launch_t<T, true, false, true, G, ONED>(a, s);
-        return a8 ? launch_t<T, true, true, true, G, ONED>(a, s) : launch_t<T, true, true, false, G, ONED>(a, s);
+    // 128 x 256 tiles of 8 waves in both rounding modes: the row-packed codes leave
+    // as whole 128-byte lines.  Up to kStripTiles of them, one wave a workgroup (a 32 x
+    // 128 strip): a strip alone on its SIMD takes 3-4 us where a tile's two waves a
+    // SIMD take 6 (128 x 256 float32 SR 5.8 -> 4.1 us, 1024 x 2048 bf16 SR 6.3 -> 4.7;
+    // 2000 x 2048, 128 tiles: 6.8 -> 5.8; 2048 x 4096, 256 tiles: 9.1 -> 9.7)
+    if constexpr (!G && !ONED) {
+        if (a.block == 32 && (a.rows_pad / 128) * ((a.cols_pad + 255) / 256) <= kStripTiles)
+            return launch_w<T, VEC, SR, G, 1, 1, ONED>(a, s);
     }
-    return sr ? launch_t<T, false, true, true, G, ONED>(a, s) : launch_t<T, false, false, true, G, ONED>(a, s);
+    return launch_w<T, VEC, SR, G, 4, 2, ONED>(a, s);
+}
+
+template <typename T, bool G, bool ONED>
+hipError_t launch_dtype(const QuantArgs &a, int vec, bool sr, hipStream_t s)
+{
+    switch (vec) {
+    case 2: return sr ? launch_t<T, 2, true, G, ONED>(a, s) : launch_t<T, 2, false, G, ONED>(a, s);
+    case 1: return sr ? launch_t<T, 1, true, G, ONED>(a, s) : launch_t<T, 1, false, G, ONED>(a, s);
+    default: return sr ? launch_t<T, 0, true, G, ONED>(a, s) : launch_t<T, 0, false, G, ONED>(a, s);
+    }
 }
 
 }  // namespace
 
 hipError_t launch_fp4_quantize(const QuantArgs &a, int dtype_bytes, bool sr, bool oned, hipStream_t stream)
 {
-    const uintptr_t base = reinterpret_cast<uintptr_t>(a.x);
-    const bool vec = a.stride_c == 1 && (base % 16) == 0 && ((a.stride_r * dtype_bytes) % 16) == 0;
-    const bool a8 = (a.stride_r % 8) == 0 && (a.index_base % 8) == 0;
+    // contiguous rows of any pitch and alignment take the vector loads (SR up to
+    // storage index 2^35, a Philox block past the end included); 2: rows start on
+    // 16-byte boundaries and, for SR, on Philox blocks
+    int vec = 0;
+    if (a.stride_c == 1 && (!sr || a.index_base + a.rows * a.stride_r + a.cols < (int64_t(1) << 35) - 4096)) {
+        const bool aligned = reinterpret_cast<uintptr_t>(a.x) % 16 == 0 && (a.stride_r * dtype_bytes) % 16 == 0;
+        const bool a8 = a.stride_r % 8 == 0 && a.index_base % 8 == 0;
+        vec = aligned && (a8 || !sr) ? 2 : a.cols >= 8 ? 1 : 0;
+    }
     const bool grouped = a.seg_offsets != nullptr;
     if (oned) {
         if (grouped) return hipErrorInvalidValue;
-        return dtype_bytes == 4 ? launch_dtype<float, false, true>(a, vec, sr, a8, stream)
-                                : launch_dtype<uint16_t, false, true>(a, vec, sr, a8, stream);
+        return dtype_bytes == 4 ? launch_dtype<float, false, true>(a, vec, sr, stream)
+                                : launch_dtype<uint16_t, false, true>(a, vec, sr, stream);
     }
     if (dtype_bytes == 4)
-        return grouped ? launch_dtype<float, true, false>(a, vec, sr, a8, stream)
-                       : launch_dtype<float, false, false>(a, vec, sr, a8, stream);
-    return grouped ? launch_dtype<uint16_t, true, false>(a, vec, sr, a8, stream)
-                   : launch_dtype<uint16_t, false, false>(a, vec, sr, a8, stream);
+        return grouped ? launch_dtype<float, true, false>(a, vec, sr, stream)
+                       : launch_dtype<float, false, false>(a, vec, sr, stream);
+    return grouped ? launch_dtype<uint16_t, true, false>(a, vec, sr, stream)
+                   : launch_dtype<uint16_t, false, false>(a, vec, sr, stream);
 }
 
 }  // namespace q2d

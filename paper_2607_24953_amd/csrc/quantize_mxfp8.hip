@@ -24,14 +24,6 @@ namespace {
 constexpr int kTile = 128;
 
 typedef short s2v __attribute__((ext_vector_type(2)));
-typedef unsigned int u4v __attribute__((ext_vector_type(4)));
-
-// 16-byte streaming load (the input is read once)
-__device__ __forceinline__ uint4 load_stream16(const void *p)
-{
-    const u4v v = __builtin_nontemporal_load(reinterpret_cast<const u4v *>(p));
-    return make_uint4(v.x, v.y, v.z, v.w);
-}
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 
 __device__ __forceinline__ uint32_t load_bits(const void *x, bool is_f32, int64_t idx)
@@ -56,7 +48,9 @@ __device__ __forceinline__ uint32_t fp8_pair_f32(uint32_t old, uint32_t lo, uint
     return __builtin_bit_cast(uint32_t, r);
 }
 
-template <bool F32, bool VEC>
+// VEC: 0 -- element by element; 1 -- contiguous rows of any pitch and alignment; 2 -- rows
+// on 16-byte boundaries
+template <bool F32, int VEC>
 __global__ __launch_bounds__(256) void mxfp8_quantize_kernel(const QuantArgs a)
 {
     constexpr bool PK = !F32;                 // bf16: two elements per register
@@ -73,35 +67,19 @@ __global__ __launch_bounds__(256) void mxfp8_quantize_kernel(const QuantArgs a)
 
     // ---- load the 8 x 8 sub-block (0 outside R x C)
     uint32_t v[8][NV];
-    if (VEC && c0 + 8 <= a.cols) {
-        const uint8_t *xr = reinterpret_cast<const uint8_t *>(a.x) + (r0 * a.stride_r + c0) * (F32 ? 4 : 2);
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            uint4 q0 = make_uint4(0u, 0u, 0u, 0u), q1 = q0;
-            if (r0 + i < a.rows) {
-                q0 = load_stream16(xr);
-                if (F32) q1 = load_stream16(xr + 16);
-            }
-            v[i][0] = q0.x; v[i][1] = q0.y; v[i][2] = q0.z; v[i][3] = q0.w;
-            if (F32) { v[i][NV - 4] = q1.x; v[i][NV - 3] = q1.y; v[i][NV - 2] = q1.z; v[i][NV - 1] = q1.w; }
-            xr += a.stride_r * (F32 ? 4 : 2);
-        }
+    if constexpr (VEC != 0) {
+        constexpr int E = F32 ? 4 : 2;
+        load_sub_block<E, VEC == 2>(v, reinterpret_cast<const uint8_t *>(a.x) + (r0 * a.stride_r + c0) * E, a.stride_r * E,
+                                    a.rows - r0, a.cols - c0);
     } else {
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
             const int64_t r = r0 + i;
+            auto at = [&](int64_t c) __attribute__((always_inline)) -> uint32_t {
+                return r < a.rows && c < a.cols ? load_bits(a.x, F32, r * a.stride_r + c * a.stride_c) : 0u;
+            };
 #pragma unroll
-            for (int k = 0; k < NV; ++k) {
-                if (PK) {
-                    const int64_t c = c0 + 2 * k;
-                    const uint32_t lo = (r < a.rows && c < a.cols) ? load_bits(a.x, false, r * a.stride_r + c * a.stride_c) : 0u;
-                    const uint32_t hi = (r < a.rows && c + 1 < a.cols) ? load_bits(a.x, false, r * a.stride_r + (c + 1) * a.stride_c) : 0u;
-                    v[i][k] = (lo >> 16) | hi;
-                } else {
-                    const int64_t c = c0 + k;
-                    v[i][k] = (r < a.rows && c < a.cols) ? load_bits(a.x, true, r * a.stride_r + c * a.stride_c) : 0u;
-                }
-            }
+            for (int k = 0; k < NV; ++k) v[i][k] = PK ? (at(c0 + 2 * k) >> 16) | at(c0 + 2 * k + 1) : at(c0 + k);
         }
     }
     // float32 bit pattern of element (i, j)
@@ -221,16 +199,17 @@ __global__ __launch_bounds__(256) void mxfp8_quantize_kernel(const QuantArgs a)
 
 hipError_t launch_mxfp8_quantize(const QuantArgs &a, int dtype_bytes, hipStream_t stream)
 {
-    const int64_t nb = (a.rows_pad / kTile) * (a.cols_pad / kTile);
-    const uintptr_t base = reinterpret_cast<uintptr_t>(a.x);
-    const bool vec = a.stride_c == 1 && (base % 16) == 0 && ((a.stride_r * dtype_bytes) % 16) == 0;
-    const dim3 grid((unsigned)nb), block(256);
+    const dim3 grid((unsigned)((a.rows_pad / kTile) * (a.cols_pad / kTile))), block(256);
+    const bool aligned = reinterpret_cast<uintptr_t>(a.x) % 16 == 0 && (a.stride_r * dtype_bytes) % 16 == 0;
+    const int vec = a.stride_c != 1 ? 0 : aligned ? 2 : a.cols >= 8 ? 1 : 0;
     if (dtype_bytes == 4) {
-        if (vec) hipLaunchKernelGGL((mxfp8_quantize_kernel<true, true>), grid, block, 0, stream, a);
-        else hipLaunchKernelGGL((mxfp8_quantize_kernel<true, false>), grid, block, 0, stream, a);
+        if (vec == 2) hipLaunchKernelGGL((mxfp8_quantize_kernel<true, 2>), grid, block, 0, stream, a);
+        else if (vec == 1) hipLaunchKernelGGL((mxfp8_quantize_kernel<true, 1>), grid, block, 0, stream, a);
+        else hipLaunchKernelGGL((mxfp8_quantize_kernel<true, 0>), grid, block, 0, stream, a);
     } else {
-        if (vec) hipLaunchKernelGGL((mxfp8_quantize_kernel<false, true>), grid, block, 0, stream, a);
-        else hipLaunchKernelGGL((mxfp8_quantize_kernel<false, false>), grid, block, 0, stream, a);
+        if (vec == 2) hipLaunchKernelGGL((mxfp8_quantize_kernel<false, 2>), grid, block, 0, stream, a);
+        else if (vec == 1) hipLaunchKernelGGL((mxfp8_quantize_kernel<false, 1>), grid, block, 0, stream, a);
+        else hipLaunchKernelGGL((mxfp8_quantize_kernel<false, 0>), grid, block, 0, stream, a);
     }
     return hipGetLastError();
 }
