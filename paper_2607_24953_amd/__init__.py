@@ -9,6 +9,7 @@ fallback: importing this package without the built library raises.
 from __future__ import annotations
 
 import ctypes
+import functools
 import os
 
 import torch
@@ -85,23 +86,61 @@ def _check(status: int, what: str):
         raise Q2DError("%s: %s (status %d)" % (what, q2d_status_string(status), status))
 
 
-def _stream(device) -> ctypes.c_void_p:
-    return ctypes.c_void_p(torch.cuda.current_stream(device).cuda_stream)
+# current stream of a device as an integer, without building a torch.cuda.Stream
+# (about 1.5 us of a call)
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
+def _stream(device) -> int:
+    if _raw_stream is None or device.index is None:
+        return torch.cuda.current_stream(device).cuda_stream
+    return _raw_stream(device.index)
+
+
+_DTYPE_CODES = {torch.float32: _F32, torch.bfloat16: _BF16}
 
 
 def _dtype_code(t: torch.dtype) -> int:
-    if t == torch.float32:
-        return _F32
-    if t == torch.bfloat16:
-        return _BF16
-    raise Q2DError("unsupported dtype %s (float32 or bfloat16)" % t)
+    try:
+        return _DTYPE_CODES[t]
+    except KeyError:
+        raise Q2DError("unsupported dtype %s (float32 or bfloat16)" % t) from None
+
+
+_BUFFERS = ("codes", "codes_t", "scales", "scales_t")
+
+
+@functools.lru_cache(maxsize=1024)
+def _layout(fmt: int, rows: int, cols: int, block: int, nseg: int | None, orientations: tuple):
+    """Layout of a quantized tensor, from its sizes alone: the descriptor's bytes (no
+    buffers), the bytes of the allocation, and name -> (offset, shape) of the
+    buffers that are wanted, each on a 256-byte boundary."""
+    d = _Tensor()
+    sizes = (ctypes.c_int64 * 4)()
+    if nseg is None:
+        _check(_lib.q2d_tensor_init(ctypes.byref(d), fmt, rows, cols, block, sizes), "q2d_tensor_init")
+    else:
+        if fmt != FP4_2D:
+            raise Q2DError("grouped tensors are 2D-block FP4 only")
+        _check(_lib.q2d_grouped_tensor_init(ctypes.byref(d), rows, cols, nseg, block, sizes),
+               "q2d_grouped_tensor_init")
+    wanted = (orientations[0], orientations[1], orientations[0], orientations[1])
+    parts, total = {}, 0
+    for name, size, want in zip(_BUFFERS, sizes, wanted):
+        if want:
+            ld = getattr(d, "ld_" + name)
+            parts[name] = (total, (size // ld, ld))
+            total += (size + 255) // 256 * 256
+    return bytes(d), d.rows, total, parts
 
 
 class QTensor:
     """A quantized matrix in both orientations (device buffers + C descriptor).
 
     ``codes``/``scales`` hold the row-major copy, ``codes_t``/``scales_t`` the
-    transposed one; each is a 2-D uint8 tensor of shape (rows, leading dim).
+    transposed one; each is a 2-D uint8 tensor of shape (rows, leading dim), or
+    None where that orientation is not wanted.  They are parts of one allocation
+    and are made when first asked for.
 
     With ``nseg`` set it is the padded grouped form of ``rows`` rows cut into
     ``nseg`` segments: ``rows`` is then the padded capacity and
@@ -109,32 +148,29 @@ class QTensor:
 
     def __init__(self, fmt: int, rows: int, cols: int, device, block: int = 32,
                  orientations=(True, True), nseg: int | None = None):
-        self.desc = _Tensor()
-        sizes = (ctypes.c_int64 * 4)()
-        if nseg is None:
-            _check(_lib.q2d_tensor_init(ctypes.byref(self.desc), fmt, rows, cols, block, sizes),
-                   "q2d_tensor_init")
-        else:
-            if fmt != FP4_2D:
-                raise Q2DError("grouped tensors are 2D-block FP4 only")
-            _check(_lib.q2d_grouped_tensor_init(ctypes.byref(self.desc), rows, cols, nseg, block,
-                                                sizes), "q2d_grouped_tensor_init")
-        d = self.desc
-        self.fmt, self.rows, self.cols, self.device = fmt, d.rows, cols, torch.device(device)
+        template, stored_rows, total, self._parts = _layout(fmt, rows, cols, block, nseg, tuple(orientations))
+        d = self.desc = _Tensor.from_buffer_copy(template)
+        self._ref = ctypes.byref(d)
+        self.fmt, self.rows, self.cols, self.device = fmt, stored_rows, cols, torch.device(device)
         self.total_rows, self.nseg = rows, nseg
-        shapes = {"codes": (sizes[0] // d.ld_codes, d.ld_codes),
-                  "codes_t": (sizes[1] // d.ld_codes_t, d.ld_codes_t),
-                  "scales": (sizes[2] // d.ld_scales, d.ld_scales),
-                  "scales_t": (sizes[3] // d.ld_scales_t, d.ld_scales_t)}
-        want = {"codes": orientations[0], "scales": orientations[0],
-                "codes_t": orientations[1], "scales_t": orientations[1]}
-        for k, shp in shapes.items():
-            t = torch.empty(shp, dtype=torch.uint8, device=self.device) if want[k] else None
-            setattr(self, k, t)
-            setattr(d, k, t.data_ptr() if t is not None else None)
+        self._buffer = torch.empty(total, dtype=torch.uint8, device=self.device)
+        base = self._buffer.data_ptr()
+        for name, (offset, _) in self._parts.items():
+            setattr(d, name, base + offset)
+
+    def __getattr__(self, name):
+        if name not in _BUFFERS:
+            raise AttributeError(name)
+        part = self._parts.get(name)
+        t = None
+        if part is not None:
+            offset, shape = part
+            t = self._buffer[offset:offset + shape[0] * shape[1]].view(shape)
+        setattr(self, name, t)
+        return t
 
     def ptr(self):
-        return ctypes.byref(self.desc)
+        return self._ref
 
 
 def q2d_tensor_init(fmt: int, rows: int, cols: int, device, block: int = 32) -> QTensor:
@@ -156,12 +192,11 @@ def _norm(device) -> torch.device:
 def _same_device(device, *objs):
     """Every tensor / QTensor in objs (None skipped) lives on `device`, a GPU: the
     kernels write through these pointers, so a host buffer must not reach them."""
-    ref = _norm(device)
-    if ref.type != "cuda":
-        raise Q2DError("expected device tensors, got %s" % ref)
+    if device.type != "cuda":
+        raise Q2DError("expected device tensors, got %s" % device)
     for o in objs:
-        if o is not None and _norm(o.device) != ref:
-            raise Q2DError("all operands must be on %s (got %s)" % (ref, o.device))
+        if o is not None and o.device != device and _norm(o.device) != _norm(device):
+            raise Q2DError("all operands must be on %s (got %s)" % (_norm(device), o.device))
 
 
 def q2d_quantize(x: torch.Tensor, mode="rtn", seed: int = 0, offset: int = 0,
