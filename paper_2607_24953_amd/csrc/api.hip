@@ -104,6 +104,7 @@ QuantArgs make_quant_args(const void *x, int64_t R, int64_t C, int64_t sr, int64
     a.store_rows = a.rows;
     a.block = 32;
     a.floor_scale = 0;
+    a.also = nullptr;
     return a;
 }
 
@@ -174,10 +175,10 @@ q2d_status q2d_tensor_init(q2d_tensor *t, q2d_fmt fmt, int64_t rows, int64_t col
 
 // The entry points below check every argument before they launch; with
 // go == false they only check (the composite linear-layer calls check all of
-// their steps before the first launch).
+// their steps before the first launch) and leave the launch arguments in *args.
 static q2d_status quantize_impl(const void *x, q2d_dtype dt, int64_t rows, int64_t cols, int64_t stride_r,
                                 int64_t stride_c, int32_t block, q2d_round mode, uint64_t seed, uint64_t offset,
-                                q2d_tensor *out, hipStream_t stream, bool go)
+                                q2d_tensor *out, hipStream_t stream, bool go, QuantArgs *args = nullptr)
 {
     q2d_status s = check_input(x, dt, rows, cols, stride_r, stride_c);
     if (s != Q2D_OK) return s;
@@ -190,6 +191,7 @@ static q2d_status quantize_impl(const void *x, q2d_dtype dt, int64_t rows, int64
     QuantArgs a = make_quant_args(x, rows, cols, stride_r, stride_c, seed, offset, out);
     a.block = block;
     a.floor_scale = ((int)mode & Q2D_FLOOR_SCALE) != 0;
+    if (args) *args = a;
     if (go && launch_fp4_quantize(a, dtype_bytes(dt), rmode == Q2D_SR, false, stream) != hipSuccess)
         return Q2D_ELAUNCH;
     return Q2D_OK;
@@ -247,7 +249,7 @@ q2d_status mxfp8_quantize(const void *x, q2d_dtype dt, int64_t rows, int64_t col
     a.scales_t = out->scales_t; a.ld_scales_t = out->ld_scales_t;
     a.rows_pad = rup(rows, 128); a.cols_pad = rup(cols, 128);
     a.nbr = rows; a.nbc = cols;
-    a.seg_offsets = nullptr; a.nseg = 0; a.store_rows = rows; a.block = 32;
+    a.seg_offsets = nullptr; a.nseg = 0; a.store_rows = rows; a.block = 32; a.floor_scale = 0; a.also = nullptr;
     if (launch_mxfp8_quantize(a, dtype_bytes(dt), stream) != hipSuccess) return Q2D_ELAUNCH;
     return Q2D_OK;
 }
@@ -362,13 +364,23 @@ q2d_status q2d_linear_fwd(const void *X, const void *W, q2d_dtype dt, int64_t T,
                           hipStream_t stream)
 {
     if (!qX || !qW || !qX->codes || !qW->codes) return Q2D_EINVAL;
-    // every step is checked (go = false) before the first one is launched
+    // every step is checked (go = false) before the first one is launched; two 2D
+    // quantizations with the same rounding go out together
+    QuantArgs ax, aw;
+    const bool oned = qX->fmt == Q2D_FMT_FP4_1D;
+    const bool both = !oned && ((int)mode_x & ~Q2D_FLOOR_SCALE) == ((int)mode_w & ~Q2D_FLOOR_SCALE);
     for (const bool go : {false, true}) {
-        q2d_status s = qX->fmt == Q2D_FMT_FP4_1D
-                           ? quantize_1d_impl(X, dt, T, K, K, 1, 32, mode_x, seed, offset_x, qX, stream, go)
-                           : quantize_impl(X, dt, T, K, K, 1, qX->block, mode_x, seed, offset_x, qX, stream, go);
-        if (s == Q2D_OK) s = quantize_impl(W, dt, N, K, K, 1, qW->block, mode_w, seed, offset_w, qW, stream, go);
-        if (s == Q2D_OK) s = gemm_impl(qX, 0, qW, 0, Y, y_dt, N, 0, stream, go);
+        if (go && both) {
+            ax.also = &aw;
+            if (launch_fp4_quantize(ax, dtype_bytes(dt), ((int)mode_x & ~Q2D_FLOOR_SCALE) == Q2D_SR, false, stream) != hipSuccess)
+                return Q2D_ELAUNCH;
+        } else {
+            q2d_status s = oned ? quantize_1d_impl(X, dt, T, K, K, 1, 32, mode_x, seed, offset_x, qX, stream, go)
+                                : quantize_impl(X, dt, T, K, K, 1, qX->block, mode_x, seed, offset_x, qX, stream, go, &ax);
+            if (s == Q2D_OK) s = quantize_impl(W, dt, N, K, K, 1, qW->block, mode_w, seed, offset_w, qW, stream, go, &aw);
+            if (s != Q2D_OK) return s;
+        }
+        const q2d_status s = gemm_impl(qX, 0, qW, 0, Y, y_dt, N, 0, stream, go);
         if (s != Q2D_OK) return s;
     }
     return Q2D_OK;

@@ -33,6 +33,9 @@ struct QuantArgs {
     int64_t store_rows;            // rows of codes / scales written (>= rows; padded rows get zeros)
     int32_t block;                 // 2D block edge: 32, or 64 (its scale written to the four 32-entries)
     int32_t floor_scale;           // 2D FP4: floor scale rule with saturation instead of the truncation-free one
+    // A second dense 2D FP4 quantization of the same element type and rounding, in
+    // the same launch where the two can share a kernel (read on the host only).
+    const QuantArgs *also;
 };
 
 // 2D blocks, or 1D blocks (oned: 1 x 32 rowwise copy, 32 x 1 colwise copy)

@@ -571,13 +571,13 @@ __device__ __forceinline__ void quantize_tile(QuantArgs a, const int64_t tr, con
 // lines end up evicted by the streaming traffic.
 template <typename T, int VEC, bool SR, int WR, bool GROUPED, int WC, bool ONED>
 __global__ __launch_bounds__(64 * WR * WC)
-__attribute__((amdgpu_waves_per_eu(VEC && SR ? (ONED && VEC == 1 ? 2 : 3) : (VEC ? 4 : 1)))) void fp4_quantize_kernel(QuantArgs a)
+__attribute__((amdgpu_waves_per_eu(VEC && SR ? (ONED && VEC == 1 ? 2 : 3) : (VEC ? 4 : 1)))) void fp4_quantize_kernel(QuantArgs a, QuantArgs a2, uint32_t first)
 {
     static_assert(!(ONED && GROUPED), "grouped tensors use 2D blocks");
     static_assert(WR == 4 || (WR == 1 && !ONED && !GROUPED), "a strip of its own: dense 2D blocks of 32");
     constexpr int kTC = 128 * WC, kTile = 32 * WR;
-    const int64_t tiles_c = (a.cols_pad + kTC - 1) / kTC;
     if constexpr (GROUPED) {
+        const int64_t tiles_c = (a.cols_pad + kTC - 1) / kTC;
         // padded start rows of the segments, built once per workgroup; the
         // workgroup then walks the row tiles of all segments (tile = blockIdx.x,
         // + gridDim.x, ...) and narrows `a` to each tile's segment
@@ -612,37 +612,46 @@ __attribute__((amdgpu_waves_per_eu(VEC && SR ? (ONED && VEC == 1 ? 2 : 3) : (VEC
             __syncthreads();                // the tile's LDS staging is reused by the next
         }
     } else {
-        const int64_t tile = blockIdx.x;
-        const int64_t tr = tile / tiles_c;
-        quantize_tile<T, VEC, SR, WR, GROUPED, WC, ONED>(a, tr, tile - tr * tiles_c);
+        // workgroups from `first` on belong to the second tensor of the launch
+        const bool second = blockIdx.x >= first;
+        const QuantArgs &b = second ? a2 : a;
+        const uint32_t tile = blockIdx.x - (second ? first : 0u), tiles_c = (uint32_t)((b.cols_pad + kTC - 1) / kTC);
+        const uint32_t tr = tile / tiles_c;
+        quantize_tile<T, VEC, SR, WR, GROUPED, WC, ONED>(b, tr, tile - tr * tiles_c);
     }
 }
 
+// 128 x 256 tiles of a quantization
+int64_t tiles_of(const QuantArgs &a) { return (a.rows_pad / 128) * ((a.cols_pad + 255) / 256); }
+
 template <typename T, int VEC, bool SR, bool G, int WR, int WC, bool ONED>
-hipError_t launch_w(const QuantArgs &a, hipStream_t s)
+hipError_t launch_w(const QuantArgs &a, const QuantArgs *a2, hipStream_t s)
 {
-    int64_t nb = (a.rows_pad / (32 * WR)) * ((a.cols_pad + 128 * WC - 1) / (128 * WC));
+    auto blocks = [](const QuantArgs &q) { return (q.rows_pad / (32 * WR)) * ((q.cols_pad + 128 * WC - 1) / (128 * WC)); };
+    int64_t nb = blocks(a);
     // grouped: each workgroup walks several tiles, so that the segment table is
     // built once per few tiles (the bound covers every padded segment's tiles);
     // 8 per CU keeps the last round of tiles short
     if (G) nb = nb < 8 * (int64_t)cu_count() ? nb : 8 * (int64_t)cu_count();
+    const int64_t all = nb + (a2 ? blocks(*a2) : 0);
+    if (all > INT32_MAX) return hipErrorInvalidValue;           // (beyond any device's memory)
     // an input larger than the 256 MB Infinity Cache streams from HBM, and two
     // workgroups (16 waves) a CU read it faster than the three or four that fit: 128.6
     // against 134 us for 16384 x 12288 bf16, round to nearest (129.4 against 138,
     // stochastic); below that size more waves hide more latency (8192 x 5632 SR: 31.5
     // against 33.8 us).  Unused dynamic LDS holds the others off.
     constexpr int kStatic = G ? 42516 : 34368;
-    const bool streams = WR == 4 && a.rows * a.cols * (int64_t)sizeof(T) > (int64_t(256) << 20);
-    const unsigned lds = streams ? (unsigned)(80000 - kStatic) : 0;
-    hipLaunchKernelGGL((fp4_quantize_kernel<T, VEC, SR, WR, G, WC, ONED>), dim3((unsigned)nb), dim3(64 * WR * WC), lds, s,
-                       a);
+    auto streams = [](const QuantArgs &q) { return q.rows * q.cols * (int64_t)sizeof(T) > (int64_t(256) << 20); };
+    const unsigned lds = WR == 4 && (streams(a) || (a2 && streams(*a2))) ? (unsigned)(80000 - kStatic) : 0;
+    hipLaunchKernelGGL((fp4_quantize_kernel<T, VEC, SR, WR, G, WC, ONED>), dim3((unsigned)all), dim3(64 * WR * WC), lds, s,
+                       a, a2 ? *a2 : a, (uint32_t)nb);
     return hipGetLastError();
 }
 
 constexpr int64_t kStripTiles = 128;
 
 template <typename T, int VEC, bool SR, bool G, bool ONED>
-hipError_t launch_t(const QuantArgs &a, hipStream_t s)
+hipError_t launch_t(const QuantArgs &a, const QuantArgs *a2, hipStream_t s)
 {
     // 128 x 256 tiles of 8 waves in both rounding modes: the row-packed codes leave
     // as whole 128-byte lines.  Up to kStripTiles of them, one wave a workgroup (a 32 x
@@ -650,46 +659,65 @@ hipError_t launch_t(const QuantArgs &a, hipStream_t s)
     // SIMD take 6 (128 x 256 float32 SR 5.8 -> 4.1 us, 1024 x 2048 bf16 SR 6.3 -> 4.7;
     // 2000 x 2048, 128 tiles: 6.8 -> 5.8; 2048 x 4096, 256 tiles: 9.1 -> 9.7)
     if constexpr (!G && !ONED) {
-        if (a.block == 32 && (a.rows_pad / 128) * ((a.cols_pad + 255) / 256) <= kStripTiles)
-            return launch_w<T, VEC, SR, G, 1, 1, ONED>(a, s);
+        if (a.block == 32 && (!a2 || a2->block == 32) && tiles_of(a) + (a2 ? tiles_of(*a2) : 0) <= kStripTiles)
+            return launch_w<T, VEC, SR, G, 1, 1, ONED>(a, a2, s);
     }
-    return launch_w<T, VEC, SR, G, 4, 2, ONED>(a, s);
+    return launch_w<T, VEC, SR, G, 4, 2, ONED>(a, a2, s);
 }
 
 template <typename T, bool G, bool ONED>
-hipError_t launch_dtype(const QuantArgs &a, int vec, bool sr, hipStream_t s)
+hipError_t launch_dtype(const QuantArgs &a, const QuantArgs *a2, int vec, bool sr, hipStream_t s)
 {
     switch (vec) {
-    case 2: return sr ? launch_t<T, 2, true, G, ONED>(a, s) : launch_t<T, 2, false, G, ONED>(a, s);
-    case 1: return sr ? launch_t<T, 1, true, G, ONED>(a, s) : launch_t<T, 1, false, G, ONED>(a, s);
-    default: return sr ? launch_t<T, 0, true, G, ONED>(a, s) : launch_t<T, 0, false, G, ONED>(a, s);
+    case 2: return sr ? launch_t<T, 2, true, G, ONED>(a, a2, s) : launch_t<T, 2, false, G, ONED>(a, a2, s);
+    case 1: return sr ? launch_t<T, 1, true, G, ONED>(a, a2, s) : launch_t<T, 1, false, G, ONED>(a, a2, s);
+    default: return sr ? launch_t<T, 0, true, G, ONED>(a, a2, s) : launch_t<T, 0, false, G, ONED>(a, a2, s);
     }
+}
+
+// How a tensor's rows can be read: contiguous rows of any pitch and alignment take
+// the vector loads (SR up to storage index 2^35, a Philox block past the end
+// included); 2: rows start on 16-byte boundaries and, for SR, on Philox blocks.
+int vec_of(const QuantArgs &a, int dtype_bytes, bool sr)
+{
+    if (a.stride_c != 1 || (sr && a.index_base + a.rows * a.stride_r + a.cols >= (int64_t(1) << 35) - 4096)) return 0;
+    const bool aligned = reinterpret_cast<uintptr_t>(a.x) % 16 == 0 && (a.stride_r * dtype_bytes) % 16 == 0;
+    const bool a8 = a.stride_r % 8 == 0 && a.index_base % 8 == 0;
+    return aligned && (a8 || !sr) ? 2 : a.cols >= 8 ? 1 : 0;
 }
 
 }  // namespace
 
 hipError_t launch_fp4_quantize(const QuantArgs &a, int dtype_bytes, bool sr, bool oned, hipStream_t stream)
 {
-    // contiguous rows of any pitch and alignment take the vector loads (SR up to
-    // storage index 2^35, a Philox block past the end included); 2: rows start on
-    // 16-byte boundaries and, for SR, on Philox blocks
-    int vec = 0;
-    if (a.stride_c == 1 && (!sr || a.index_base + a.rows * a.stride_r + a.cols < (int64_t(1) << 35) - 4096)) {
-        const bool aligned = reinterpret_cast<uintptr_t>(a.x) % 16 == 0 && (a.stride_r * dtype_bytes) % 16 == 0;
-        const bool a8 = a.stride_r % 8 == 0 && a.index_base % 8 == 0;
-        vec = aligned && (a8 || !sr) ? 2 : a.cols >= 8 ? 1 : 0;
+    const int vec = vec_of(a, dtype_bytes, sr);
+    if (a.also) {
+        // Two tensors in one launch: the second one's tiles fill the CUs that the
+        // first one's last round leaves, and a launch (3 us of the host, 2-3 us of the
+        // device) is saved: 8192 x 2048 and 5632 x 2048 bf16 SR 30.9 -> 27 us.  Beyond
+        // 128 MB together they are better read one after the other (16384 x 4096 and
+        // 12288 x 4096: 4 us slower in one launch).
+        QuantArgs one = a;
+        one.also = nullptr;
+        const int64_t bytes = (a.rows * a.cols + a.also->rows * a.also->cols) * dtype_bytes;
+        if (vec != vec_of(*a.also, dtype_bytes, sr) || bytes > (int64_t(128) << 20)) {
+            const hipError_t e = launch_fp4_quantize(one, dtype_bytes, sr, false, stream);
+            return e != hipSuccess ? e : launch_fp4_quantize(*a.also, dtype_bytes, sr, false, stream);
+        }
+        return dtype_bytes == 4 ? launch_dtype<float, false, false>(one, a.also, vec, sr, stream)
+                                : launch_dtype<uint16_t, false, false>(one, a.also, vec, sr, stream);
     }
     const bool grouped = a.seg_offsets != nullptr;
     if (oned) {
         if (grouped) return hipErrorInvalidValue;
-        return dtype_bytes == 4 ? launch_dtype<float, false, true>(a, vec, sr, stream)
-                                : launch_dtype<uint16_t, false, true>(a, vec, sr, stream);
+        return dtype_bytes == 4 ? launch_dtype<float, false, true>(a, nullptr, vec, sr, stream)
+                                : launch_dtype<uint16_t, false, true>(a, nullptr, vec, sr, stream);
     }
     if (dtype_bytes == 4)
-        return grouped ? launch_dtype<float, true, false>(a, vec, sr, stream)
-                       : launch_dtype<float, false, false>(a, vec, sr, stream);
-    return grouped ? launch_dtype<uint16_t, true, false>(a, vec, sr, stream)
-                   : launch_dtype<uint16_t, false, false>(a, vec, sr, stream);
+        return grouped ? launch_dtype<float, true, false>(a, nullptr, vec, sr, stream)
+                       : launch_dtype<float, false, false>(a, nullptr, vec, sr, stream);
+    return grouped ? launch_dtype<uint16_t, true, false>(a, nullptr, vec, sr, stream)
+                   : launch_dtype<uint16_t, false, false>(a, nullptr, vec, sr, stream);
 }
 
 }  // namespace q2d
