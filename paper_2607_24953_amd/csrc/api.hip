@@ -305,7 +305,8 @@ static q2d_status gemm_operands(const q2d_tensor *A, int transA, const q2d_tenso
 }
 
 static q2d_status gemm_impl(const q2d_tensor *A, int transA, const q2d_tensor *B, int transB, void *C,
-                            q2d_dtype c_dt, int64_t ldc, int accumulate, hipStream_t stream, bool go)
+                            q2d_dtype c_dt, int64_t ldc, int accumulate, hipStream_t stream, bool go,
+                            GemmArgs *args = nullptr)
 {
     if (!A || !B || !C || !valid_dtype(c_dt)) return Q2D_EINVAL;
     if (accumulate != 0 && accumulate != 1) return Q2D_EINVAL;
@@ -317,6 +318,7 @@ static q2d_status gemm_impl(const q2d_tensor *A, int transA, const q2d_tensor *B
     if (!aligned(C, (uintptr_t)dtype_bytes(c_dt))) return Q2D_EINVAL;
     g.c = C; g.ldc = ldc;
     g.accumulate = accumulate;
+    if (args) *args = g;
     if (go && launch_gemm(g, fp4 ? kFmtFp4Block2D : kFmtMxfp8, c_dt == Q2D_BF16, stream) != hipSuccess)
         return Q2D_ELAUNCH;
     return Q2D_OK;
@@ -394,11 +396,19 @@ q2d_status q2d_linear_bwd(const void *dY, q2d_dtype dt, const q2d_tensor *qX, co
     const int64_t T = qX->rows, K = qX->cols, N = qW->rows;
     if (qW->cols != K || qdY->rows != T || qdY->cols != N) return Q2D_EINVAL;
     if (!qdY->codes || !qdY->codes_t || !qX->codes_t || !qW->codes_t) return Q2D_EINVAL;
+    // every step is checked before the first one is launched; the two products go out
+    // together
     for (const bool go : {false, true}) {
+        GemmArgs gx, gw;
         q2d_status s = quantize_impl(dY, dt, T, N, N, 1, qdY->block, mode_dy, seed, offset_dy, qdY, stream, go);
-        if (s == Q2D_OK) s = gemm_impl(qdY, 0, qW, 1, dX, dx_dt, K, 0, stream, go);
-        if (s == Q2D_OK) s = gemm_impl(qdY, 1, qX, 1, dW, dw_dt, K, accumulate_dw, stream, go);
+        if (s == Q2D_OK) s = gemm_impl(qdY, 0, qW, 1, dX, dx_dt, K, 0, stream, false, &gx);
+        if (s == Q2D_OK) s = gemm_impl(qdY, 1, qX, 1, dW, dw_dt, K, accumulate_dw, stream, false, &gw);
         if (s != Q2D_OK) return s;
+        if (!go) continue;
+        gx.also = &gw;
+        gx.also_bf16 = dw_dt == Q2D_BF16;
+        // (the formats are FP4: quantize_impl has checked dY's, and operands pair only so)
+        if (launch_gemm(gx, kFmtFp4Block2D, dx_dt == Q2D_BF16, stream) != hipSuccess) return Q2D_ELAUNCH;
     }
     return Q2D_OK;
 }

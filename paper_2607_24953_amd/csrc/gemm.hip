@@ -1150,8 +1150,16 @@ hipError_t launch_gemm(const GemmArgs &g, int fmt, int c_is_bf16, hipStream_t st
 {
     // the 256 x 256 kernels address each operand with 32-bit byte offsets from the
     // K-tile base
-    const bool off32 = g.M * g.lda <= (int64_t(1) << 32) && g.N * g.ldb <= (int64_t(1) << 32);
-    const SmallTile tile = pick_tile(g, fmt, off32);
+    auto off32 = [](const GemmArgs &x) { return x.M * x.lda <= (int64_t(1) << 32) && x.N * x.ldb <= (int64_t(1) << 32); };
+    if (g.also) {
+        GemmArgs one = g, two = *g.also;
+        one.also = two.also = nullptr;
+        hipError_t e = launch_gemm_pair(g, c_is_bf16, off32(g) && off32(two), stream);
+        if (e != hipErrorNotSupported) return e;
+        e = launch_gemm(one, fmt, c_is_bf16, stream);
+        return e != hipSuccess ? e : launch_gemm(two, fmt, g.also_bf16, stream);
+    }
+    const SmallTile tile = pick_tile(g, fmt, off32(g), nullptr);
     if (tile != kTile256) return launch_gemm_small(g, fmt, c_is_bf16, tile, stream);
     const int tm = (int)((g.M + BM2 - 1) / BM2), tn = (int)((g.N + BN2 - 1) / BN2);
     if (fmt == kFmtFp4Block2D)

@@ -170,8 +170,16 @@ __device__ __forceinline__ int swz128(int r)
 // stage s + 1.  WM: how the scale words come: 0 -- both operands in 2D blocks: each
 // wave loads its own block rows' words of both units at once; 1 -- one word per
 // row (1D blocks, MXFP8).
+template <int FMT, int TI, int TJ, int RING, int WM>
+constexpr int tile_lds_bytes()
+{
+    const int rows = 64 * (TI + TJ);
+    return RING * (128 * rows + (WM ? 4 * (FMT == kFmtMxfp8 ? 1 : 2) * rows : 4 * 256));
+}
+
 template <int FMT, int TI, int TJ, int RING, int WM, bool BF16OUT>
-__global__ __launch_bounds__(kThreads, 1) void gemm_tile_kernel(const GemmArgs g, uint32_t tiles_m, uint32_t tiles_n)
+__device__ __forceinline__ void gemm_tile(const GemmArgs &g, uint8_t *smem, uint32_t block, uint32_t tiles_m,
+                                          uint32_t tiles_n)
 {
     constexpr bool F8 = FMT == kFmtMxfp8;
     constexpr int TM = 64 * TI, TN = 64 * TJ, kRows = TM + TN;
@@ -182,10 +190,10 @@ __global__ __launch_bounds__(kThreads, 1) void gemm_tile_kernel(const GemmArgs g
     constexpr int CODES = kRows / 32, WORDS = WM ? WU * WG : 1; // this wave's loads per stage
     constexpr int LOADS = CODES + WORDS, H1 = (LOADS + 1) / 2;  // the first H1 in the second unit
     static_assert(WM || !F8, "MXFP8 has one word per row");
-    __shared__ __attribute__((aligned(1024))) uint8_t smem[RING * kStage];
+    static_assert(RING * kStage == tile_lds_bytes<FMT, TI, TJ, RING, WM>(), "the caller's LDS");
 
     uint32_t tm, tn;
-    tile_coords_of(blockIdx.x, tiles_m, tiles_n, 8u, tm, tn);
+    tile_coords_of(block, tiles_m, tiles_n, 8u, tm, tn);
     const int64_t m0 = (int64_t)tm * TM, n0 = (int64_t)tn * TN;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int wm = wave >> 1, wn = wave & 1, half = lane >> 5;
@@ -375,20 +383,28 @@ __global__ __launch_bounds__(kThreads, 1) void gemm_tile_kernel(const GemmArgs g
 }
 
 // (32 TI) x (32 TJ) tiles, TI = TJ, K split over the four waves in whole units of 128.
+template <int TI, int TJ>
+constexpr int ksplit_lds_bytes()
+{
+    const int rows = 32 * (TI + TJ), waves = kThreads / 64;
+    const int ring = waves * kRing * (rows * 64 + (rows + 63) / 64 * 256), red = waves * TI * TJ * 4 * 64 * 16;
+    return ring > red ? ring : red;
+}
+
 template <int FMT, int TI, int TJ, bool BF16OUT>
-__global__ __launch_bounds__(kThreads, 1) void gemm_ksplit_kernel(const GemmArgs g, uint32_t tiles_m, uint32_t tiles_n)
+__device__ __forceinline__ void gemm_ksplit(const GemmArgs &g, uint8_t *smem, uint32_t block, uint32_t tiles_m,
+                                            uint32_t tiles_n)
 {
     constexpr int kWaves = kThreads / 64;
     constexpr int kRows = 32 * (TI + TJ);
     constexpr int CODES = kRows / 16, WORDS = (kRows + 63) / 64;        // loads per wave and stage
     constexpr int kStage = kRows * 64 + WORDS * 256;            // per wave
     constexpr bool PAIR = BF16OUT && TJ == 2;                   // interleaved output columns
-    constexpr int kRed = kWaves * TI * TJ * 4 * 64 * 16;        // partial tiles at the end
-    constexpr int kLds = kWaves * kRing * kStage > kRed ? kWaves * kRing * kStage : kRed;
-    __shared__ __attribute__((aligned(1024))) uint8_t smem[kLds];
+    static_assert(kWaves * kRing * kStage <= ksplit_lds_bytes<TI, TJ>() &&
+                  kWaves * TI * TJ * 4 * 64 * 16 <= ksplit_lds_bytes<TI, TJ>(), "rings, then partial tiles");
 
     uint32_t tm, tn;
-    tile_coords_of(blockIdx.x, tiles_m, tiles_n, 8u, tm, tn);
+    tile_coords_of(block, tiles_m, tiles_n, 8u, tm, tn);
     const int64_t m0 = (int64_t)tm * 32 * TI, n0 = (int64_t)tn * 32 * TJ;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int half = lane >> 5;
@@ -537,36 +553,87 @@ __global__ __launch_bounds__(kThreads, 1) void gemm_ksplit_kernel(const GemmArgs
     }
 }
 
-template <int FMT, int TI, int TJ, int RING, bool BF>
-hipError_t launch_tile(const GemmArgs &g, hipStream_t s)
-{
-    const int64_t tm = (g.M + 64 * TI - 1) / (64 * TI), tn = (g.N + 64 * TJ - 1) / (64 * TJ);
-    const dim3 grid((unsigned)(tm * tn)), block(kThreads);
-    if (FMT == kFmtMxfp8 || g.a1d || g.b1d)
-        hipLaunchKernelGGL((gemm_tile_kernel<FMT, TI, TJ, RING, 1, BF>), grid, block, 0, s, g, (uint32_t)tm, (uint32_t)tn);
-    else if constexpr (FMT != kFmtMxfp8)
-        hipLaunchKernelGGL((gemm_tile_kernel<FMT, TI, TJ, RING, 0, BF>), grid, block, 0, s, g, (uint32_t)tm, (uint32_t)tn);
-    return hipGetLastError();
-}
+// The tiles of one product, or of two in one grid (workgroups from `first` on belong
+// to the second).  BF0, BF1: bf16 outputs.
+struct Pair {
+    GemmArgs g[2];
+    uint32_t first;
+    uint32_t tiles_m[2], tiles_n[2];
+};
 
-template <int FMT, int TI, int TJ, bool BF>
-hipError_t launch_ksplit(const GemmArgs &g, hipStream_t s)
+template <int FMT, int TI, int TJ, int RING, int WM, bool BF0, bool BF1>
+__global__ __launch_bounds__(kThreads, 1) void gemm_tile_kernel(const Pair p)
 {
-    const int64_t tm = (g.M + 32 * TI - 1) / (32 * TI), tn = (g.N + 32 * TJ - 1) / (32 * TJ);
-    hipLaunchKernelGGL((gemm_ksplit_kernel<FMT, TI, TJ, BF>), dim3((unsigned)(tm * tn)), dim3(kThreads), 0, s, g,
-                       (uint32_t)tm, (uint32_t)tn);
-    return hipGetLastError();
-}
-
-template <int FMT, bool BF>
-hipError_t launch_t(const GemmArgs &g, SmallTile tile, hipStream_t s)
-{
-    switch (tile) {
-    case kTile32: return launch_ksplit<FMT, 1, 1, BF>(g, s);
-    case kTile64: return launch_ksplit<FMT, 2, 2, BF>(g, s);
-    case kTile128: return launch_tile<FMT, 2, 2, 3, BF>(g, s);
-    default: return launch_tile<FMT, 4, 2, 3, BF>(g, s);
+    __shared__ __attribute__((aligned(1024))) uint8_t smem[tile_lds_bytes<FMT, TI, TJ, RING, WM>()];
+    const bool second = blockIdx.x >= p.first;
+    if constexpr (BF0 == BF1) {
+        const int i = second ? 1 : 0;
+        gemm_tile<FMT, TI, TJ, RING, WM, BF0>(p.g[i], smem, blockIdx.x - (second ? p.first : 0u), p.tiles_m[i], p.tiles_n[i]);
+    } else {
+        if (!second) gemm_tile<FMT, TI, TJ, RING, WM, BF0>(p.g[0], smem, blockIdx.x, p.tiles_m[0], p.tiles_n[0]);
+        else gemm_tile<FMT, TI, TJ, RING, WM, BF1>(p.g[1], smem, blockIdx.x - p.first, p.tiles_m[1], p.tiles_n[1]);
     }
+}
+
+template <int FMT, int TI, int TJ, bool BF0, bool BF1>
+__global__ __launch_bounds__(kThreads, 1) void gemm_ksplit_kernel(const Pair p)
+{
+    __shared__ __attribute__((aligned(1024))) uint8_t smem[ksplit_lds_bytes<TI, TJ>()];
+    const bool second = blockIdx.x >= p.first;
+    if constexpr (BF0 == BF1) {
+        const int i = second ? 1 : 0;
+        gemm_ksplit<FMT, TI, TJ, BF0>(p.g[i], smem, blockIdx.x - (second ? p.first : 0u), p.tiles_m[i], p.tiles_n[i]);
+    } else {
+        if (!second) gemm_ksplit<FMT, TI, TJ, BF0>(p.g[0], smem, blockIdx.x, p.tiles_m[0], p.tiles_n[0]);
+        else gemm_ksplit<FMT, TI, TJ, BF1>(p.g[1], smem, blockIdx.x - p.first, p.tiles_m[1], p.tiles_n[1]);
+    }
+}
+
+constexpr struct { int32_t tm, tn, per_cu; } kTiles[] = {{32, 32, 2}, {64, 64, 1}, {128, 128, 1}, {256, 128, 1}, {256, 256, 1}};
+
+int64_t tiles_of(const GemmArgs &g, int tile)
+{
+    return ((g.M + kTiles[tile].tm - 1) / kTiles[tile].tm) * ((g.N + kTiles[tile].tn - 1) / kTiles[tile].tn);
+}
+
+template <int FMT, bool BF0, bool BF1>
+hipError_t launch_t(const GemmArgs &a, const GemmArgs *b, int tile, hipStream_t s)
+{
+    Pair p;
+    p.g[0] = a;
+    p.g[1] = b ? *b : a;
+    p.first = (uint32_t)tiles_of(a, tile);
+    for (int i = 0; i < 2; ++i) {
+        p.tiles_m[i] = (uint32_t)((p.g[i].M + kTiles[tile].tm - 1) / kTiles[tile].tm);
+        p.tiles_n[i] = (uint32_t)((p.g[i].N + kTiles[tile].tn - 1) / kTiles[tile].tn);
+    }
+    const dim3 grid((unsigned)(tiles_of(a, tile) + (b ? tiles_of(*b, tile) : 0))), block(kThreads);
+    const bool rowwise = FMT == kFmtMxfp8 || a.a1d || a.b1d || (b && (b->a1d || b->b1d));
+    switch (tile) {
+    case kTile32: hipLaunchKernelGGL((gemm_ksplit_kernel<FMT, 1, 1, BF0, BF1>), grid, block, 0, s, p); break;
+    case kTile64: hipLaunchKernelGGL((gemm_ksplit_kernel<FMT, 2, 2, BF0, BF1>), grid, block, 0, s, p); break;
+    case kTile128:
+        if (rowwise) hipLaunchKernelGGL((gemm_tile_kernel<FMT, 2, 2, 3, 1, BF0, BF1>), grid, block, 0, s, p);
+        else if constexpr (FMT != kFmtMxfp8) hipLaunchKernelGGL((gemm_tile_kernel<FMT, 2, 2, 3, 0, BF0, BF1>), grid, block, 0, s, p);
+        break;
+    default:
+        if (rowwise) hipLaunchKernelGGL((gemm_tile_kernel<FMT, 4, 2, 3, 1, BF0, BF1>), grid, block, 0, s, p);
+        else if constexpr (FMT != kFmtMxfp8) hipLaunchKernelGGL((gemm_tile_kernel<FMT, 4, 2, 3, 0, BF0, BF1>), grid, block, 0, s, p);
+    }
+    return hipGetLastError();
+}
+
+// Modelled microseconds of `tiles` tiles with `units` 128-value units of K each (see
+// pick_tile), without the launch itself.
+float cost_of(int tile, int64_t tiles, float units, int fmt)
+{
+    static const struct { float once, round, unit[2]; } cost[] = {{0.0f, 1.0f, {0.14f, 0.22f}},     // unit: FP4, MXFP8
+                                                                  {0.0f, 2.0f, {0.21f, 0.375f}},
+                                                                  {0.0f, 3.0f, {0.29f, 0.55f}},
+                                                                  {0.0f, 5.5f, {0.47f, 0.90f}},
+                                                                  {4.0f, 5.0f, {0.82f, 1.55f}}};
+    const int64_t slots = (int64_t)cu_count() * kTiles[tile].per_cu;
+    return cost[tile].once + (float)((tiles + slots - 1) / slots) * (cost[tile].round + units * cost[tile].unit[fmt == kFmtMxfp8]);
 }
 
 }  // namespace
@@ -581,32 +648,55 @@ hipError_t launch_t(const GemmArgs &g, SmallTile tile, hipStream_t s)
 // 18.6 / 12.1 / 16.5 / 26.7; 2048 x 4096 x 4096 72 / 65 / 25.4 / 22.9 / 27.6; 777 x
 // 11008 x 4096 76 / 72 / 34 / 34 / 29; 4096 x 4096 x 4096 139 / 125 / 51 / 45 / 37.
 // `large`: the 256 x 256 kernels can take the problem.
-SmallTile pick_tile(const GemmArgs &g, int fmt, bool large)
+SmallTile pick_tile(const GemmArgs &g, int fmt, bool large, float *time)
 {
-    struct Cost { int32_t tm, tn, per_cu; float once, round, unit[2]; };      // unit: FP4, MXFP8
-    static const Cost cost[] = {{32, 32, 2, 0.0f, 1.0f, {0.14f, 0.22f}},
-                                {64, 64, 1, 0.0f, 2.0f, {0.21f, 0.375f}},
-                                {128, 128, 1, 0.0f, 3.0f, {0.29f, 0.55f}},
-                                {256, 128, 1, 0.0f, 5.5f, {0.47f, 0.90f}},
-                                {256, 256, 1, 4.0f, 5.0f, {0.82f, 1.55f}}};
-    const int64_t cus = cu_count(), units = g.K / 128;
     const int top = large ? kTile256 : kTile256x128;
     int best = top;
     float least = 0.0f;
     for (int k = top; k >= 0; --k) {
-        const Cost &c = cost[k];
-        const int64_t tiles = ((g.M + c.tm - 1) / c.tm) * ((g.N + c.tn - 1) / c.tn), slots = cus * c.per_cu;
-        const float t = c.once + (float)((tiles + slots - 1) / slots) * (c.round + (float)units * c.unit[fmt == kFmtMxfp8]);
+        const float t = cost_of(k, tiles_of(g, k), (float)(g.K / 128), fmt);
         if (k == top || t < least) { best = k; least = t; }
     }
+    if (time) *time = least;
     return (SmallTile)best;
 }
 
 hipError_t launch_gemm_small(const GemmArgs &g, int fmt, int c_is_bf16, SmallTile tile, hipStream_t stream)
 {
     if (fmt == kFmtFp4Block2D)
-        return c_is_bf16 ? launch_t<kFmtFp4Block2D, true>(g, tile, stream) : launch_t<kFmtFp4Block2D, false>(g, tile, stream);
-    return c_is_bf16 ? launch_t<kFmtMxfp8, true>(g, tile, stream) : launch_t<kFmtMxfp8, false>(g, tile, stream);
+        return c_is_bf16 ? launch_t<kFmtFp4Block2D, true, true>(g, nullptr, tile, stream)
+                         : launch_t<kFmtFp4Block2D, false, false>(g, nullptr, tile, stream);
+    return c_is_bf16 ? launch_t<kFmtMxfp8, true, true>(g, nullptr, tile, stream)
+                     : launch_t<kFmtMxfp8, false, false>(g, nullptr, tile, stream);
+}
+
+// Two FP4 products in one grid of small tiles, where the model finds that no slower
+// than a launch each: the launch (2.5 us of the device, 3 of the host) is saved and
+// the second product fills the CUs that the first one's last round leaves.  One
+// round lasts as long as its longest K; over several rounds K averages out.
+// hipErrorNotSupported: not taken.
+hipError_t launch_gemm_pair(const GemmArgs &g, int c_is_bf16, bool large, hipStream_t stream)
+{
+    const GemmArgs &h = *g.also;
+    if (g.also_bf16 && !c_is_bf16) return hipErrorNotSupported;        // (no kernel for that order)
+    float t0 = 0.0f, t1 = 0.0f;
+    pick_tile(g, kFmtFp4Block2D, large, &t0);
+    pick_tile(h, kFmtFp4Block2D, large, &t1);
+    int best = -1;
+    float least = t0 + t1 + 2.5f;
+    for (int k = kTile256x128; k >= 0; --k) {
+        const int64_t n0 = tiles_of(g, k), n1 = tiles_of(h, k), slots = (int64_t)cu_count() * kTiles[k].per_cu;
+        const float u0 = (float)(g.K / 128), u1 = (float)(h.K / 128);
+        const float units = n0 + n1 <= slots ? (u0 > u1 ? u0 : u1) : ((float)n0 * u0 + (float)n1 * u1) / (float)(n0 + n1);
+        const float t = cost_of(k, n0 + n1, units, kFmtFp4Block2D);
+        if (t < least) { best = k; least = t; }
+    }
+    if (best < 0) return hipErrorNotSupported;
+    GemmArgs a = g, b = h;
+    a.also = b.also = nullptr;
+    if (c_is_bf16) return g.also_bf16 ? launch_t<kFmtFp4Block2D, true, true>(a, &b, best, stream)
+                                      : launch_t<kFmtFp4Block2D, true, false>(a, &b, best, stream);
+    return launch_t<kFmtFp4Block2D, false, false>(a, &b, best, stream);
 }
 
 }  // namespace q2d

@@ -63,6 +63,10 @@ struct GemmArgs {
     // 16-bit value of storage index r * N + c from the Philox stream (seed, offset)
     int qsr;
     uint64_t seed, offset;
+    // a second, independent FP4 product, in the same launch where that is faster
+    // (read on the host only)
+    const GemmArgs *also;
+    int also_bf16;                      // its c is bf16
 };
 
 enum GemmFmt { kFmtFp4Block2D = 0, kFmtMxfp8 = 1 };
@@ -76,8 +80,10 @@ hipError_t launch_gemm(const GemmArgs &g, int fmt, int c_is_bf16, hipStream_t st
 // problem, and the 256 x 256 kernels.
 enum SmallTile { kTile32 = 0, kTile64 = 1, kTile128 = 2, kTile256x128 = 3, kTile256 = 4 };
 
-SmallTile pick_tile(const GemmArgs &g, int fmt, bool large);
+// (time: the modelled microseconds)
+SmallTile pick_tile(const GemmArgs &g, int fmt, bool large, float *time);
 hipError_t launch_gemm_small(const GemmArgs &g, int fmt, int c_is_bf16, SmallTile tile, hipStream_t stream);
+hipError_t launch_gemm_pair(const GemmArgs &g, int c_is_bf16, bool large, hipStream_t stream);
 
 // Grouped (MoE) GEMMs over nseg experts with device segment offsets.
 //   ragged M: A = grouped rows (padded), op(B) of expert e is rows

@@ -635,13 +635,13 @@ hipError_t launch_w(const QuantArgs &a, const QuantArgs *a2, hipStream_t s)
     if (G) nb = nb < 8 * (int64_t)cu_count() ? nb : 8 * (int64_t)cu_count();
     const int64_t all = nb + (a2 ? blocks(*a2) : 0);
     if (all > INT32_MAX) return hipErrorInvalidValue;           // (beyond any device's memory)
-    // an input larger than the 256 MB Infinity Cache streams from HBM, and two
-    // workgroups (16 waves) a CU read it faster than the three or four that fit: 128.6
-    // against 134 us for 16384 x 12288 bf16, round to nearest (129.4 against 138,
-    // stochastic); below that size more waves hide more latency (8192 x 5632 SR: 31.5
-    // against 33.8 us).  Unused dynamic LDS holds the others off.
+    // an input of 96 MB or more streams from HBM, and two workgroups (16 waves) a CU
+    // read it faster than the three or four that fit: 128.6 against 134 us for 16384 x
+    // 12288 bf16, round to nearest (129.4 against 138, stochastic); below that size
+    // more waves hide more latency (8192 x 5632 SR: 31.5 against 33.8 us).  Unused
+    // dynamic LDS holds the others off.
     constexpr int kStatic = G ? 42516 : 34368;
-    auto streams = [](const QuantArgs &q) { return q.rows * q.cols * (int64_t)sizeof(T) > (int64_t(256) << 20); };
+    auto streams = [](const QuantArgs &q) { return q.rows * q.cols * (int64_t)sizeof(T) >= (int64_t(96) << 20); };
     const unsigned lds = WR == 4 && (streams(a) || (a2 && streams(*a2))) ? (unsigned)(80000 - kStatic) : 0;
     hipLaunchKernelGGL((fp4_quantize_kernel<T, VEC, SR, WR, G, WC, ONED>), dim3((unsigned)all), dim3(64 * WR * WC), lds, s,
                        a, a2 ? *a2 : a, (uint32_t)nb);
