@@ -211,6 +211,8 @@ def kind_of(kernel_name: str):
         return {"0": "gemm_fp4", "1": "gemm_fp4_grouped"}.get(a[2], "gemm_fp4_grouped_k")
     if "gemm_fp8_256_kernel" in kernel_name:
         return "gemm_fp8"
+    if "gemm_tile_grouped_kernel" in kernel_name:
+        return "gemm_fp4_grouped"
     m = re.search(r"gemm_(?:tile_|ksplit_)?kernel<(\d)", kernel_name)
     if m:
         return "gemm_fp4" if m.group(1) == "0" else "gemm_fp8"

@@ -1229,6 +1229,14 @@ hipError_t launch_grouped_gemm(const GemmArgs &g, const GroupedArgs &gr, int c_i
 {
     const int tn = (int)((g.N + BN2 - 1) / BN2);
     if (!gr.ragged_k) {
+        // up to two rounds of 256 x 256 tiles, about half a tile an expert being padding:
+        // the 128 x 128 tiles lose less to padding and to the last round (6000 rows of 32
+        // experts, N = K = 1024: 15.8 against 19.9 us; 16000 rows of 64, N = 768: 23.6
+        // against 35.8; 600 rows of 8, N = 1536, K = 2048: 12 against 22).  Beyond, the
+        // persistent tiles move fewer operand bytes (32768 rows of 16, N = 1024, K = 2048:
+        // 58 against 69; 131072 rows of 128, N = 1536: 292 against 360)
+        if ((gr.total_rows / BM2 + gr.nseg / 2) * tn <= 2 * (int64_t)cu_count())
+            return launch_grouped_small(g, gr, c_is_bf16, stream);
         // row tiles over all experts: at most total_rows / 256 + nseg
         const int rt = (int)((gr.total_rows + BM2 - 1) / BM2) + gr.nseg;
         return c_is_bf16 ? launch_persistent<true, 1>(g, gr, 0, tn, (int64_t)rt * tn, stream)

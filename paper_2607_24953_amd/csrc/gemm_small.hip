@@ -4,8 +4,8 @@
 // Both kernels stage XOR-swizzled operand rows in LDS with the global -> LDS loads
 // of the large-tile kernels.
 //
-// gemm_tile_kernel: 128 x 128 or 256 x 128 tiles, 2 x 2 waves, a ring of three
-// stages shared by the workgroup.  What bounds it: at 256 workgroups the loads --
+// gemm_tile_kernel: 128 x 128 tiles, 2 x 2 waves, a ring of three stages shared by
+// the workgroup, or of two with two workgroups a CU.  What bounds it: at 256 workgroups the loads --
 // an L2 channel serves one request a cycle whether it is 64 or 128 bytes, so
 // stages hold whole 128-byte lines (with 64-byte rows a stage of 128 values took
 // 920 cycles against 650-720 on 2048 x 4096 x 4096), and a load instruction costs
@@ -178,8 +178,7 @@ constexpr int tile_lds_bytes()
 }
 
 template <int FMT, int TI, int TJ, int RING, int WM, bool BF16OUT>
-__device__ __forceinline__ void gemm_tile(const GemmArgs &g, uint8_t *smem, uint32_t block, uint32_t tiles_m,
-                                          uint32_t tiles_n)
+__device__ __forceinline__ void gemm_tile(const GemmArgs &g, uint8_t *smem, uint32_t tm, uint32_t tn)
 {
     constexpr bool F8 = FMT == kFmtMxfp8;
     constexpr int TM = 64 * TI, TN = 64 * TJ, kRows = TM + TN;
@@ -192,8 +191,6 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &g, uint8_t *smem, uint
     static_assert(WM || !F8, "MXFP8 has one word per row");
     static_assert(RING * kStage == tile_lds_bytes<FMT, TI, TJ, RING, WM>(), "the caller's LDS");
 
-    uint32_t tm, tn;
-    tile_coords_of(block, tiles_m, tiles_n, 8u, tm, tn);
     const int64_t m0 = (int64_t)tm * TM, n0 = (int64_t)tn * TN;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int wm = wave >> 1, wn = wave & 1, half = lane >> 5;
@@ -562,16 +559,61 @@ struct Pair {
 };
 
 template <int FMT, int TI, int TJ, int RING, int WM, bool BF0, bool BF1>
-__global__ __launch_bounds__(kThreads, 1) void gemm_tile_kernel(const Pair p)
+__global__ __launch_bounds__(kThreads, RING == 2 ? 2 : 1) void gemm_tile_kernel(const Pair p)
 {
     __shared__ __attribute__((aligned(1024))) uint8_t smem[tile_lds_bytes<FMT, TI, TJ, RING, WM>()];
     const bool second = blockIdx.x >= p.first;
-    if constexpr (BF0 == BF1) {
-        const int i = second ? 1 : 0;
-        gemm_tile<FMT, TI, TJ, RING, WM, BF0>(p.g[i], smem, blockIdx.x - (second ? p.first : 0u), p.tiles_m[i], p.tiles_n[i]);
-    } else {
-        if (!second) gemm_tile<FMT, TI, TJ, RING, WM, BF0>(p.g[0], smem, blockIdx.x, p.tiles_m[0], p.tiles_n[0]);
-        else gemm_tile<FMT, TI, TJ, RING, WM, BF1>(p.g[1], smem, blockIdx.x - p.first, p.tiles_m[1], p.tiles_n[1]);
+    const int i = second ? 1 : 0;
+    uint32_t tm, tn;
+    tile_coords_of(blockIdx.x - (second ? p.first : 0u), p.tiles_m[i], p.tiles_n[i], 8u, tm, tn);
+    if (BF0 == BF1 || !second) gemm_tile<FMT, TI, TJ, RING, WM, BF0>(p.g[BF0 == BF1 ? i : 0], smem, tm, tn);
+    else gemm_tile<FMT, TI, TJ, RING, WM, BF1>(p.g[1], smem, tm, tn);
+}
+
+// Ragged-M grouped (MoE) product on 128 x 128 tiles, two workgroups a CU, each
+// walking row tiles of all experts x column tiles.
+template <bool BF16OUT>
+__global__ __launch_bounds__(kThreads, 2) void gemm_tile_grouped_kernel(const GemmArgs g, const GroupedArgs gr,
+                                                                       uint32_t tiles_n)
+{
+    __shared__ __attribute__((aligned(1024))) uint8_t smem[tile_lds_bytes<kFmtFp4Block2D, 2, 2, 2, 0>()];
+    __shared__ int32_t seg_start[kMaxSegs + 1], pad_start[kMaxSegs + 1], tile_start[kMaxSegs + 1];
+    if ((threadIdx.x >> 6) == 0) {
+        wave_offsets(gr.nseg, gr.seg_offsets, gr.total_rows, seg_start);
+        __builtin_amdgcn_wave_barrier();
+        const int32_t *off = seg_start;
+        wave_prefix(gr.nseg, [&](int i) { return (off[i + 1] - off[i] + 127) / 128 * 128; }, pad_start);
+        wave_prefix(gr.nseg, [&](int i) { return (off[i + 1] - off[i] + 127) / 128; }, tile_start);
+    }
+    __syncthreads();
+    const uint32_t total = (uint32_t)__builtin_amdgcn_readfirstlane(tile_start[gr.nseg]) * tiles_n;
+    for (uint32_t u = blockIdx.x; u < total; u += gridDim.x) {
+        // as in the persistent kernel: a multiple of 8 column tiles already gives each
+        // XCD one column band; otherwise a contiguous range of the order
+        uint32_t tt = u;
+        if (tiles_n % kXcds != 0) {
+            const uint32_t xcd = u % kXcds, local = u / kXcds, per = total / kXcds, rem = total % kXcds;
+            tt = xcd * per + (xcd < rem ? xcd : rem) + local;
+        }
+        const uint32_t rt = tt / tiles_n, tn = tt - rt * tiles_n;
+        const int e = __builtin_amdgcn_readfirstlane(seg_search(tile_start, gr.nseg, (int32_t)rt));
+        const uint32_t tm = rt - (uint32_t)__builtin_amdgcn_readfirstlane(tile_start[e]);
+        const int64_t p_e = __builtin_amdgcn_readfirstlane(pad_start[e]);
+        const int64_t o0 = __builtin_amdgcn_readfirstlane(seg_start[e]);
+        GemmArgs t = g;
+        t.M = __builtin_amdgcn_readfirstlane(seg_start[e + 1]) - o0;
+        t.a += p_e * g.lda;
+        t.sa += (p_e / 32) * g.ldsa;
+        t.c = reinterpret_cast<uint8_t *>(t.c) + o0 * g.ldc * (BF16OUT ? 2 : 4);
+        if (gr.b_group_rows) {
+            t.b += (int64_t)e * gr.b_group_rows * g.ldb;
+            t.sb += ((int64_t)e * gr.b_group_rows / 32) * g.ldsb;
+        } else {
+            t.b += (int64_t)e * gr.b_group_k / 2;
+            t.sb += (int64_t)e * gr.b_group_k / 32;
+        }
+        gemm_tile<kFmtFp4Block2D, 2, 2, 2, 0, BF16OUT>(t, smem, tm, tn);
+        __syncthreads();                                // the tile's LDS is the next one's
     }
 }
 
@@ -589,7 +631,7 @@ __global__ __launch_bounds__(kThreads, 1) void gemm_ksplit_kernel(const Pair p)
     }
 }
 
-constexpr struct { int32_t tm, tn, per_cu; } kTiles[] = {{32, 32, 2}, {64, 64, 1}, {128, 128, 1}, {256, 128, 1}, {256, 256, 1}};
+constexpr struct { int32_t tm, tn, per_cu; } kTiles[] = {{32, 32, 2}, {64, 64, 1}, {128, 128, 1}, {128, 128, 2}, {256, 256, 1}};
 
 int64_t tiles_of(const GemmArgs &g, int tile)
 {
@@ -617,8 +659,8 @@ hipError_t launch_t(const GemmArgs &a, const GemmArgs *b, int tile, hipStream_t 
         else if constexpr (FMT != kFmtMxfp8) hipLaunchKernelGGL((gemm_tile_kernel<FMT, 2, 2, 3, 0, BF0, BF1>), grid, block, 0, s, p);
         break;
     default:
-        if (rowwise) hipLaunchKernelGGL((gemm_tile_kernel<FMT, 4, 2, 3, 1, BF0, BF1>), grid, block, 0, s, p);
-        else if constexpr (FMT != kFmtMxfp8) hipLaunchKernelGGL((gemm_tile_kernel<FMT, 4, 2, 3, 0, BF0, BF1>), grid, block, 0, s, p);
+        if (rowwise) hipLaunchKernelGGL((gemm_tile_kernel<FMT, 2, 2, 2, 1, BF0, BF1>), grid, block, 0, s, p);
+        else if constexpr (FMT != kFmtMxfp8) hipLaunchKernelGGL((gemm_tile_kernel<FMT, 2, 2, 2, 0, BF0, BF1>), grid, block, 0, s, p);
     }
     return hipGetLastError();
 }
@@ -630,7 +672,7 @@ float cost_of(int tile, int64_t tiles, float units, int fmt)
     static const struct { float once, round, unit[2]; } cost[] = {{0.0f, 1.0f, {0.14f, 0.22f}},     // unit: FP4, MXFP8
                                                                   {0.0f, 2.0f, {0.21f, 0.375f}},
                                                                   {0.0f, 3.0f, {0.29f, 0.55f}},
-                                                                  {0.0f, 5.5f, {0.47f, 0.90f}},
+                                                                  {0.0f, 2.6f, {0.57f, 1.10f}},
                                                                   {4.0f, 5.0f, {0.82f, 1.55f}}};
     const int64_t slots = (int64_t)cu_count() * kTiles[tile].per_cu;
     return cost[tile].once + (float)((tiles + slots - 1) / slots) * (cost[tile].round + units * cost[tile].unit[fmt == kFmtMxfp8]);
@@ -639,18 +681,19 @@ float cost_of(int tile, int64_t tiles, float units, int fmt)
 }  // namespace
 
 // The tile with the smallest modelled time: rounds of workgroups over the chip
-// (the 32 x 32 kernel holds two a CU, the others one), each a fixed part (address
-// setup, first loads, epilogue) plus a part per 128 values of K; the 256 x 256
-// kernels pay some of the fixed part once.  Microseconds fitted to timings on one
-// MI355X with a launch's own 2.5 us taken off (FP4, bf16 output).  Measured with
-// tiles of 32 / 64 / 128 / 256 x 128 / 256: 600 x 700 x 128 3.1 / 4.5 / 5.7 / 8.7 /
-// 12.2 us; 128 x 4096 x 4096 7.8 / 9.2 / 11.0 / 19.6 / 30.4; 512 x 4096 x 4096 21.0 /
-// 18.6 / 12.1 / 16.5 / 26.7; 2048 x 4096 x 4096 72 / 65 / 25.4 / 22.9 / 27.6; 777 x
-// 11008 x 4096 76 / 72 / 34 / 34 / 29; 4096 x 4096 x 4096 139 / 125 / 51 / 45 / 37.
+// (kTiles: how many a CU holds), each a fixed part (address setup, first loads,
+// epilogue) plus a part per 128 values of K; the 256 x 256 kernels pay some of the
+// fixed part once.  Microseconds fitted to timings on one MI355X with a launch's
+// own 2.5 us taken off (FP4, bf16 output).  Measured with 32 / 64 / 128 / 128 two a
+// CU / 256: 600 x 700 x 128 3.1 / 4.5 / 5.7 / - / 12.2 us; 128 x 4096 x 4096 7.8 /
+// 9.2 / 11.0 / - / 30.4; 512 x 4096 x 4096 21.0 / 18.6 / 11.9 / 16.0 / 26.6; 2048 x
+// 4096 x 4096 72 / 65 / 26.7 / 23.7 / 28.9; 16384 x 2048 x 768 - / - / 35.7 / 26.4 /
+// 26.1; 4096 x 4096 x 4096 139 / 125 / 49 / 44 / 38.  (256 x 128 tiles, one a CU: 45 us
+// for the last, 42.3 against 37.8 for 16384 x 1536 x 2048.)
 // `large`: the 256 x 256 kernels can take the problem.
 SmallTile pick_tile(const GemmArgs &g, int fmt, bool large, float *time)
 {
-    const int top = large ? kTile256 : kTile256x128;
+    const int top = large ? kTile256 : kTile128x2;
     int best = top;
     float least = 0.0f;
     for (int k = top; k >= 0; --k) {
@@ -670,6 +713,20 @@ hipError_t launch_gemm_small(const GemmArgs &g, int fmt, int c_is_bf16, SmallTil
                      : launch_t<kFmtMxfp8, false, false>(g, nullptr, tile, stream);
 }
 
+hipError_t launch_grouped_small(const GemmArgs &g, const GroupedArgs &gr, int c_is_bf16, hipStream_t stream)
+{
+    const uint32_t tn = (uint32_t)((g.N + 127) / 128);
+    const int64_t tiles = ((gr.total_rows + 127) / 128 + gr.nseg) * (int64_t)tn;       // at most
+    int64_t grid = 2 * (int64_t)cu_count();
+    grid = grid < tiles ? grid : tiles;
+    grid = (grid + kXcds - 1) / kXcds * kXcds;
+    if (c_is_bf16)
+        hipLaunchKernelGGL((gemm_tile_grouped_kernel<true>), dim3((unsigned)grid), dim3(kThreads), 0, stream, g, gr, tn);
+    else
+        hipLaunchKernelGGL((gemm_tile_grouped_kernel<false>), dim3((unsigned)grid), dim3(kThreads), 0, stream, g, gr, tn);
+    return hipGetLastError();
+}
+
 // Two FP4 products in one grid of small tiles, where the model finds that no slower
 // than a launch each: the launch (2.5 us of the device, 3 of the host) is saved and
 // the second product fills the CUs that the first one's last round leaves.  One
@@ -684,7 +741,7 @@ hipError_t launch_gemm_pair(const GemmArgs &g, int c_is_bf16, bool large, hipStr
     pick_tile(h, kFmtFp4Block2D, large, &t1);
     int best = -1;
     float least = t0 + t1 + 2.5f;
-    for (int k = kTile256x128; k >= 0; --k) {
+    for (int k = kTile128x2; k >= 0; --k) {
         const int64_t n0 = tiles_of(g, k), n1 = tiles_of(h, k), slots = (int64_t)cu_count() * kTiles[k].per_cu;
         const float u0 = (float)(g.K / 128), u1 = (float)(h.K / 128);
         const float units = n0 + n1 <= slots ? (u0 > u1 ? u0 : u1) : ((float)n0 * u0 + (float)n1 * u1) / (float)(n0 + n1);

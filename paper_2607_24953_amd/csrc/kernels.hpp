@@ -78,7 +78,7 @@ hipError_t launch_gemm(const GemmArgs &g, int fmt, int c_is_bf16, hipStream_t st
 
 // Output tiles of the dense GEMMs, by size: the small-tile kernels, which take any
 // problem, and the 256 x 256 kernels.
-enum SmallTile { kTile32 = 0, kTile64 = 1, kTile128 = 2, kTile256x128 = 3, kTile256 = 4 };
+enum SmallTile { kTile32 = 0, kTile64 = 1, kTile128 = 2, kTile128x2 = 3, kTile256 = 4 };
 
 // (time: the modelled microseconds)
 SmallTile pick_tile(const GemmArgs &g, int fmt, bool large, float *time);
@@ -99,6 +99,7 @@ struct GroupedArgs {
     int64_t b_group_k;         // ragged M: K columns of op(B) per expert, or 0
 };
 
+hipError_t launch_grouped_small(const GemmArgs &g, const GroupedArgs &gr, int c_is_bf16, hipStream_t stream);
 hipError_t launch_grouped_gemm(const GemmArgs &g, const GroupedArgs &gr, int c_is_bf16, hipStream_t stream);
 
 // Dequantization of one stored copy back to R x C values (row-major out).

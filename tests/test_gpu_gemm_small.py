@@ -6,8 +6,8 @@ than, equal to and longer than the LDS rings; odd numbers of units, where the la
 
 float32 outputs of FP4 operands: relative Frobenius error <= 1e-5; MXFP8: the
 elementwise bound derived from the matrix instruction's arithmetic; bf16: one
-rounding.  The size rule gives, from the top: 32 x 32, 64 x 64, 128 x 128 and
-256 x 128 tiles."""
+rounding.  The size rule gives, from the top: 32 x 32, 64 x 64, 128 x 128 tiles
+one and two a CU."""
 import numpy as np
 import pytest
 import torch
@@ -96,3 +96,42 @@ def test_small_gemm_strided_output(q2d, M, N, K, dtype, pad, base, acc):
         again = c.clone()
         q2d.q2d_gemm(qa, 0, qb, 0, out=c)
         assert torch.equal(c, again)            # the K split adds in a fixed order
+
+
+@pytest.mark.parametrize("counts,N,K", [((1, 0, 127, 128, 129, 40), 160, 384), ((300,) * 7, 640, 128),
+                                        ((0, 5, 260, 33) * 15, 1024, 640)])
+@pytest.mark.parametrize("tb", [0, 1])
+@pytest.mark.parametrize("dtype,pad", [(torch.float32, 0), (torch.bfloat16, 0), (torch.bfloat16, 1)])
+def test_small_grouped_gemm(q2d, counts, N, K, tb, dtype, pad):
+    """Ragged-M products with few tiles (128 x 128 tiles): empty experts, segments of
+    one row and around a tile, odd numbers of K units, several tiles a workgroup, an
+    odd row pitch, accumulation.  Per expert against the float64 oracle."""
+    if tb and K % 128:
+        pytest.skip("transposed weights need K of whole 128")
+    off = np.concatenate([[0], np.cumsum(counts)]).astype(np.int64)
+    E, S = len(counts), int(off[-1])
+    X = synth.normal((S, K), 1.0, S + K, torch.bfloat16, device=DEV)
+    W = synth.normal((E * K, N) if tb else (E * N, K), 0.02, N + K, torch.bfloat16, device=DEV)
+    offs = torch.from_numpy(off).to(DEV)
+    qx, qw = q2d.q2d_grouped_quantize(X, offs), q2d.q2d_quantize(W)
+    flat = synth.normal((S, N + pad), 0.5, 3, dtype, device=DEV)
+    before = flat.clone()
+    c = flat[:, :N]
+    q2d.q2d_grouped_gemm(qx, 0, qw, tb, offs, out=c)
+    got = c.clone()
+    q2d.q2d_grouped_gemm(qx, 0, qw, tb, offs, out=c, accumulate=True)
+    assert torch.equal(flat[:, N:], before[:, N:])
+    ow = oracle.operand(oracle.quantize_fp4_2d(W.cpu(), "rtn"), False)
+    for e in range(E):
+        a, b = int(off[e]), int(off[e + 1])
+        if a == b:
+            continue
+        xe = oracle.operand(oracle.quantize_fp4_2d(X[a:b].cpu().contiguous(), "rtn"), False)
+        we = ow[e * K:(e + 1) * K].T if tb else ow[e * N:(e + 1) * N]
+        ref = oracle.gemm(xe, we)
+        if dtype == torch.bfloat16:
+            check_bf16(got[a:b], ref)
+            check_bf16(c[a:b], ref + got[a:b].double().cpu().numpy())
+        else:
+            assert rel_frob(got[a:b].cpu().numpy(), ref) <= 1e-5
+            assert rel_frob(c[a:b].cpu().numpy(), 2 * ref) <= 1e-5
