@@ -213,6 +213,9 @@ def kind_of(kernel_name: str):
         return "gemm_fp8"
     if "gemm_tile_grouped_kernel" in kernel_name:
         return "gemm_fp4_grouped"
+    m = re.search(r"gemm_tile_quant_kernel<\d+, \d+, (\w+)>", kernel_name)
+    if m:
+        return "gemm_fp4_dxq" if m.group(1) == "true" else "gemm_fp4_yq"
     m = re.search(r"gemm_(?:tile_|ksplit_)?kernel<(\d)", kernel_name)
     if m:
         return "gemm_fp4" if m.group(1) == "0" else "gemm_fp8"

@@ -24,7 +24,7 @@
 // Before these kernels a 128 x 128 register-staged kernel took 47.9 us for 16 x
 // 12288 x 4096 (now 8.0), 34 us for 2000 x 2048 x 2048 (11.2), 8 us for 128 x 256
 // x 256 (2.9), kernel trace against launches in a graph.
-#include "gemm_common.hpp"
+#include "gemm_quant.hpp"
 
 namespace q2d {
 
@@ -177,7 +177,8 @@ constexpr int tile_lds_bytes()
     return RING * (128 * rows + (WM ? 4 * (FMT == kFmtMxfp8 ? 1 : 2) * rows : 4 * 256));
 }
 
-template <int FMT, int TI, int TJ, int RING, int WM, bool BF16OUT>
+// QOUT (QSR): the product leaves in FP4 (rounded stochastically) instead.
+template <int FMT, int TI, int TJ, int RING, int WM, bool BF16OUT, bool QOUT = false, bool QSR = false>
 __device__ __forceinline__ void gemm_tile(const GemmArgs &g, uint8_t *smem, uint32_t tm, uint32_t tn)
 {
     constexpr bool F8 = FMT == kFmtMxfp8;
@@ -333,6 +334,16 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &g, uint8_t *smem, uint
     // a lane holds column lane % 32 (bf16: a pair) and rows 8 q + 4 half + 0..3 of
     // every MFMA tile
     const int64_t r0 = m0 + wm * 32 * TI, c0 = n0 + wn * 32 * TJ;
+    if constexpr (QOUT) {
+        static_assert(4 * (q_strip(TJ) + kPTab) <= RING * kStage, "strips and draw tables fit the ring");
+        __syncthreads();                                // every wave has read its last stage
+        uint8_t *strip = smem + wave * (q_strip(TJ) + kPTab), *ptab = strip + q_strip(TJ);
+        if (m0 + TM <= g.M && n0 + TN <= g.N)
+            store_qblock<false, QSR, TI, TJ, false>(acc, g, strip, ptab, (int)r0, (int)c0, 32 * TI, 32 * TJ);
+        else
+            store_qblock<true, QSR, TI, TJ, false>(acc, g, strip, ptab, (int)r0, (int)c0, (int)(g.M - r0), (int)(g.N - c0));
+        return;
+    }
     if (m0 + TM <= g.M && n0 + TN <= g.N && !g.accumulate && (!BF16OUT || pair_stores(g))) {
         uint8_t *p = reinterpret_cast<uint8_t *>(g.c) + ((r0 + 4 * half) * g.ldc + c0) * (BF16OUT ? 2 : 4) + 4 * (lane & 31);
         const int64_t pitch = g.ldc * (BF16OUT ? 2 : 4);
@@ -617,6 +628,16 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_tile_grouped_kernel(const Ge
     }
 }
 
+template <int RING, int WM, bool QSR>
+__global__ __launch_bounds__(kThreads, RING == 2 ? 2 : 1) void gemm_tile_quant_kernel(const GemmArgs g, uint32_t tiles_m,
+                                                                                     uint32_t tiles_n)
+{
+    __shared__ __attribute__((aligned(1024))) uint8_t smem[tile_lds_bytes<kFmtFp4Block2D, 2, 2, RING, WM>()];
+    uint32_t tm, tn;
+    tile_coords_of(blockIdx.x, tiles_m, tiles_n, 8u, tm, tn);
+    gemm_tile<kFmtFp4Block2D, 2, 2, RING, WM, false, true, QSR>(g, smem, tm, tn);
+}
+
 template <int FMT, int TI, int TJ, bool BF0, bool BF1>
 __global__ __launch_bounds__(kThreads, 1) void gemm_ksplit_kernel(const Pair p)
 {
@@ -666,16 +687,18 @@ hipError_t launch_t(const GemmArgs &a, const GemmArgs *b, int tile, hipStream_t 
 }
 
 // Modelled microseconds of `tiles` tiles with `units` 128-value units of K each (see
-// pick_tile), without the launch itself.
-float cost_of(int tile, int64_t tiles, float units, int fmt)
+// pick_tile), without the launch itself.  epi: what the epilogue writes (0 values, 1
+// FP4 rounded to nearest, 2 FP4 rounded stochastically).
+float cost_of(int tile, int64_t tiles, float units, int fmt, int epi)
 {
-    static const struct { float once, round, unit[2]; } cost[] = {{0.0f, 1.0f, {0.14f, 0.22f}},     // unit: FP4, MXFP8
-                                                                  {0.0f, 2.0f, {0.21f, 0.375f}},
-                                                                  {0.0f, 3.0f, {0.29f, 0.55f}},
-                                                                  {0.0f, 2.6f, {0.57f, 1.10f}},
-                                                                  {4.0f, 5.0f, {0.82f, 1.55f}}};
+    static const struct { float once, round[3], unit[2]; } cost[] = {{0.0f, {1.0f, 0.0f, 0.0f}, {0.14f, 0.22f}},    // unit: FP4, MXFP8
+                                                                     {0.0f, {2.0f, 0.0f, 0.0f}, {0.21f, 0.375f}},
+                                                                     {0.0f, {3.0f, 4.5f, 6.5f}, {0.29f, 0.55f}},
+                                                                     {0.0f, {2.6f, 4.0f, 6.7f}, {0.57f, 1.10f}},
+                                                                     {4.0f, {5.0f, 11.5f, 18.5f}, {0.82f, 1.55f}}};
     const int64_t slots = (int64_t)cu_count() * kTiles[tile].per_cu;
-    return cost[tile].once + (float)((tiles + slots - 1) / slots) * (cost[tile].round + units * cost[tile].unit[fmt == kFmtMxfp8]);
+    return cost[tile].once +
+           (float)((tiles + slots - 1) / slots) * (cost[tile].round[epi] + units * cost[tile].unit[fmt == kFmtMxfp8]);
 }
 
 }  // namespace
@@ -690,14 +713,19 @@ float cost_of(int tile, int64_t tiles, float units, int fmt)
 // 4096 x 4096 72 / 65 / 26.7 / 23.7 / 28.9; 16384 x 2048 x 768 - / - / 35.7 / 26.4 /
 // 26.1; 4096 x 4096 x 4096 139 / 125 / 49 / 44 / 38.  (256 x 128 tiles, one a CU: 45 us
 // for the last, 42.3 against 37.8 for 16384 x 1536 x 2048.)
+// FP4 outputs (128 / 128 two a CU / 256, nearest): 500 x 1024 x 1024 10.1 / 9.7 / 20.9;
+// 4096 x 4096 x 512 23.2 / 15.3 / 19.3; 4096 x 4096 x 4096 54 / 47 / 45; stochastic: 12.0 /
+// 11.7 / 28.3; 30.4 / 20.6 / 26.3; 62 / 52 / 52 -- the epilogue's arithmetic leaves the
+// matrix cores idle where a CU holds one workgroup.
 // `large`: the 256 x 256 kernels can take the problem.
 SmallTile pick_tile(const GemmArgs &g, int fmt, bool large, float *time)
 {
+    const int epi = g.qc ? (g.qsr ? 2 : 1) : 0, last = epi ? kTile128 : kTile32;
     const int top = large ? kTile256 : kTile128x2;
     int best = top;
     float least = 0.0f;
-    for (int k = top; k >= 0; --k) {
-        const float t = cost_of(k, tiles_of(g, k), (float)(g.K / 128), fmt);
+    for (int k = top; k >= last; --k) {
+        const float t = cost_of(k, tiles_of(g, k), (float)(g.K / 128), fmt, epi);
         if (k == top || t < least) { best = k; least = t; }
     }
     if (time) *time = least;
@@ -711,6 +739,24 @@ hipError_t launch_gemm_small(const GemmArgs &g, int fmt, int c_is_bf16, SmallTil
                          : launch_t<kFmtFp4Block2D, false, false>(g, nullptr, tile, stream);
     return c_is_bf16 ? launch_t<kFmtMxfp8, true, true>(g, nullptr, tile, stream)
                      : launch_t<kFmtMxfp8, false, false>(g, nullptr, tile, stream);
+}
+
+hipError_t launch_quantized_small(const GemmArgs &g, SmallTile tile, hipStream_t stream)
+{
+    const uint32_t tm = (uint32_t)((g.M + 127) / 128), tn = (uint32_t)((g.N + 127) / 128);
+    const dim3 grid(tm * tn), block(kThreads);
+    const bool rowwise = g.a1d || g.b1d, two = tile == kTile128x2;
+    switch ((two ? 4 : 0) | (rowwise ? 2 : 0) | (g.qsr ? 1 : 0)) {
+    case 0: hipLaunchKernelGGL((gemm_tile_quant_kernel<3, 0, false>), grid, block, 0, stream, g, tm, tn); break;
+    case 1: hipLaunchKernelGGL((gemm_tile_quant_kernel<3, 0, true>), grid, block, 0, stream, g, tm, tn); break;
+    case 2: hipLaunchKernelGGL((gemm_tile_quant_kernel<3, 1, false>), grid, block, 0, stream, g, tm, tn); break;
+    case 3: hipLaunchKernelGGL((gemm_tile_quant_kernel<3, 1, true>), grid, block, 0, stream, g, tm, tn); break;
+    case 4: hipLaunchKernelGGL((gemm_tile_quant_kernel<2, 0, false>), grid, block, 0, stream, g, tm, tn); break;
+    case 5: hipLaunchKernelGGL((gemm_tile_quant_kernel<2, 0, true>), grid, block, 0, stream, g, tm, tn); break;
+    case 6: hipLaunchKernelGGL((gemm_tile_quant_kernel<2, 1, false>), grid, block, 0, stream, g, tm, tn); break;
+    default: hipLaunchKernelGGL((gemm_tile_quant_kernel<2, 1, true>), grid, block, 0, stream, g, tm, tn);
+    }
+    return hipGetLastError();
 }
 
 hipError_t launch_grouped_small(const GemmArgs &g, const GroupedArgs &gr, int c_is_bf16, hipStream_t stream)
@@ -745,7 +791,7 @@ hipError_t launch_gemm_pair(const GemmArgs &g, int c_is_bf16, bool large, hipStr
         const int64_t n0 = tiles_of(g, k), n1 = tiles_of(h, k), slots = (int64_t)cu_count() * kTiles[k].per_cu;
         const float u0 = (float)(g.K / 128), u1 = (float)(h.K / 128);
         const float units = n0 + n1 <= slots ? (u0 > u1 ? u0 : u1) : ((float)n0 * u0 + (float)n1 * u1) / (float)(n0 + n1);
-        const float t = cost_of(k, n0 + n1, units, kFmtFp4Block2D);
+        const float t = cost_of(k, n0 + n1, units, kFmtFp4Block2D, 0);
         if (t < least) { best = k; least = t; }
     }
     if (best < 0) return hipErrorNotSupported;

@@ -99,6 +99,7 @@ struct GroupedArgs {
     int64_t b_group_k;         // ragged M: K columns of op(B) per expert, or 0
 };
 
+hipError_t launch_quantized_small(const GemmArgs &g, SmallTile tile, hipStream_t stream);
 hipError_t launch_grouped_small(const GemmArgs &g, const GroupedArgs &gr, int c_is_bf16, hipStream_t stream);
 hipError_t launch_grouped_gemm(const GemmArgs &g, const GroupedArgs &gr, int c_is_bf16, hipStream_t stream);
 

@@ -15,7 +15,7 @@ import torch
 import fp8_mfma_model as fm
 import oracle
 import synth
-from helpers import check_bf16, rel_frob
+from helpers import assert_same_bytes, check_bf16, gpu_buffers, rel_frob
 
 pytestmark = pytest.mark.gpu
 
@@ -135,3 +135,27 @@ def test_small_grouped_gemm(q2d, counts, N, K, tb, dtype, pad):
         else:
             assert rel_frob(got[a:b].cpu().numpy(), ref) <= 1e-5
             assert rel_frob(c[a:b].cpu().numpy(), 2 * ref) <= 1e-5
+
+
+@pytest.mark.parametrize("M,N,K,fmt", [(130, 200, 384, "2d"), (700, 1032, 1300, "a1"), (1500, 3000, 640, "2d"),
+                                       (2100, 4000, 384, "b1"), (4090, 4088, 4100, "2d")])
+@pytest.mark.parametrize("mode", ["rtn", "sr"])
+def test_small_gemm_quantized(q2d, M, N, K, fmt, mode):
+    """FP4 outputs from 128 x 128 tiles, one and two workgroups a CU, and (last) from
+    the persistent kernel: operands on the E2M1 grid with unit scales make the
+    float32 sums exact, so every byte is the oracle's."""
+    rng = np.random.default_rng(M + N)
+    grid = np.array([0, .5, 1, 1.5, 2, 3, 4, 6], np.float32)
+
+    def matrix(rows):
+        x = grid[rng.integers(0, 8, (rows, K))] * rng.choice(np.array([-1, 1], np.float32), (rows, K))
+        x[::32, :] = 6.0
+        x[:, ::32] = 6.0
+        return torch.from_numpy(x)
+
+    a, b = matrix(M), matrix(N)
+    qa = q2d.q2d_quantize_1d(a.to(DEV)) if fmt == "a1" else q2d.q2d_quantize(a.to(DEV))
+    qb = q2d.q2d_quantize_1d(b.to(DEV)) if fmt == "b1" else q2d.q2d_quantize(b.to(DEV))
+    got = q2d.q2d_gemm_quantized(qa, 0, qb, 0, mode, seed=2**40 + 1, offset=9)
+    want = oracle.gemm_quantized(a.numpy().astype(np.float64), b.numpy().astype(np.float64), mode, 2**40 + 1, 9)
+    assert_same_bytes(gpu_buffers(got), want, "%s %s" % ((M, N, K), mode))
