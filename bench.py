@@ -193,7 +193,8 @@ KIND_SOURCES = {"gemm_fp4": "gemm.hip", "gemm_fp4_grouped": "gemm.hip", "gemm_fp
 
 
 def kind_hash(kind: str) -> str:
-    return source_hash(KIND_SOURCES[kind], "device_common.hpp", "kernels.hpp")
+    more = ("gemm_small.hip", "gemm_common.hpp", "gemm_quant.hpp") if KIND_SOURCES[kind] == "gemm.hip" else ()
+    return source_hash(KIND_SOURCES[kind], *more, "device_common.hpp", "kernels.hpp")
 
 
 def kind_of(kernel_name: str):

@@ -5,14 +5,15 @@
 // of the large-tile kernels.
 //
 // gemm_tile_kernel: 128 x 128 tiles, 2 x 2 waves, a ring of three stages shared by
-// the workgroup, or of two with two workgroups a CU.  What bounds it: at 256 workgroups the loads --
-// an L2 channel serves one request a cycle whether it is 64 or 128 bytes, so
-// stages hold whole 128-byte lines (with 64-byte rows a stage of 128 values took
-// 920 cycles against 650-720 on 2048 x 4096 x 4096), and a load instruction costs
-// the CU 16-20 cycles whatever its size, so 2D scale words come with one load per
-// wave and stage.  Alone on a CU it is bound by its own issue: the next fragments'
-// reads and the loads sit between MFMAs (all loads in one group: 14.4 us for 128 x
-// 4096 x 4096, spread 10.9 us).
+// the workgroup, or of two with two workgroups a CU.  What bounds it: at 256
+// workgroups the loads -- an L2 channel serves one request a cycle whether it is 64
+// or 128 bytes, so stages hold whole 128-byte lines (with 64-byte rows a stage of
+// 128 values took 920 cycles against 722 on 2048 x 4096 x 4096), and a load
+// instruction costs the CU 16-20 cycles whatever its size, so 2D scale words come
+// with one load per wave and stage (a load per 64 rows: 74 of the 722 cycles).
+// Alone on a CU it is bound by its own issue: the next fragments' reads and the
+// loads sit between MFMAs (all loads in one group: 14.4 us for 128 x 4096 x 4096,
+// spread 10.9 us).
 //
 // gemm_ksplit_kernel: 32 x 32 or 64 x 64 tiles; the four waves of a workgroup
 // split K.  Each wave runs its own ring (64-byte rows, four stages, a scale word
