@@ -569,7 +569,7 @@ __device__ __forceinline__ void quantize_tile(QuantArgs a, const int64_t tr, con
 // for round to nearest) only the float32 round-to-nearest variants reach theirs.
 // Spilled registers cost HBM writes here, not only latency: every wave's spill
 // lines end up evicted by the streaming traffic.
-template <typename T, int VEC, bool SR, int WR, bool GROUPED, int WC, bool ONED>
+template <typename T, int VEC, bool SR, int WR, bool GROUPED, int WC, bool ONED, bool PAIR>
 __global__ __launch_bounds__(64 * WR * WC)
 __attribute__((amdgpu_waves_per_eu(VEC && SR ? (ONED && VEC == 1 ? 2 : 3) : (VEC ? 4 : 1)))) void fp4_quantize_kernel(QuantArgs a, QuantArgs a2, uint32_t first)
 {
@@ -612,8 +612,11 @@ __attribute__((amdgpu_waves_per_eu(VEC && SR ? (ONED && VEC == 1 ? 2 : 3) : (VEC
             __syncthreads();                // the tile's LDS staging is reused by the next
         }
     } else {
-        // workgroups from `first` on belong to the second tensor of the launch
-        const bool second = blockIdx.x >= first;
+        // PAIR: workgroups from `first` on belong to the second tensor of the launch.  A
+        // launch of one tensor has a kernel of its own: the choice at the start of each
+        // workgroup cost it 2 % (16384 x 12288 bf16 SR 119.1 us against 116.7 for the
+        // one-tensor kernel before it, alternating; without it 115.3 against 115.5)
+        const bool second = PAIR && blockIdx.x >= first;
         const QuantArgs &b = second ? a2 : a;
         const uint32_t tile = blockIdx.x - (second ? first : 0u), tiles_c = (uint32_t)((b.cols_pad + kTC - 1) / kTC);
         const uint32_t tr = tile / tiles_c;
@@ -643,8 +646,14 @@ hipError_t launch_w(const QuantArgs &a, const QuantArgs *a2, hipStream_t s)
     constexpr int kStatic = G ? 42516 : 34368;
     auto streams = [](const QuantArgs &q) { return q.rows * q.cols * (int64_t)sizeof(T) >= (int64_t(96) << 20); };
     const unsigned lds = WR == 4 && (streams(a) || (a2 && streams(*a2))) ? (unsigned)(80000 - kStatic) : 0;
-    hipLaunchKernelGGL((fp4_quantize_kernel<T, VEC, SR, WR, G, WC, ONED>), dim3((unsigned)all), dim3(64 * WR * WC), lds, s,
-                       a, a2 ? *a2 : a, (uint32_t)nb);
+    const dim3 grid((unsigned)all), block(64 * WR * WC);
+    if constexpr (!G && !ONED) {
+        if (a2) {
+            hipLaunchKernelGGL((fp4_quantize_kernel<T, VEC, SR, WR, G, WC, ONED, true>), grid, block, lds, s, a, *a2, (uint32_t)nb);
+            return hipGetLastError();
+        }
+    }
+    hipLaunchKernelGGL((fp4_quantize_kernel<T, VEC, SR, WR, G, WC, ONED, false>), grid, block, lds, s, a, a, (uint32_t)nb);
     return hipGetLastError();
 }
 
