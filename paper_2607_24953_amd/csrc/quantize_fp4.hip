@@ -380,12 +380,14 @@ __device__ __forceinline__ void quantize_tile(QuantArgs a, const int64_t tr, con
                     // halves sh .. sh + 7 of the sixteen; sh is the same for every lane
                     // (r0 and c0 are multiples of 8)
                     const int sh = (int)((a.index_base + i * a.stride_r) & 7);
+                    // (both operands as values: a choice between array elements would keep
+                    // the array in scratch memory)
 #pragma unroll
-                    for (int j = 0; j < 6; ++j) w[j] = (sh & 4) ? w[j + 2] : w[j];
+                    for (int j = 0; j < 6; ++j) { const uint32_t a0 = w[j], a1 = w[j + 2]; w[j] = (sh & 4) ? a1 : a0; }
 #pragma unroll
-                    for (int j = 0; j < 5; ++j) w[j] = (sh & 2) ? w[j + 1] : w[j];
+                    for (int j = 0; j < 5; ++j) { const uint32_t a0 = w[j], a1 = w[j + 1]; w[j] = (sh & 2) ? a1 : a0; }
 #pragma unroll
-                    for (int j = 0; j < 4; ++j) w[j] = (sh & 1) ? (w[j] >> 16) | (w[j + 1] << 16) : w[j];
+                    for (int j = 0; j < 4; ++j) { const uint32_t a0 = w[j], a1 = w[j + 1]; w[j] = (sh & 1) ? (a0 >> 16) | (a1 << 16) : a0; }
                 }
             }
 #pragma unroll

@@ -1,0 +1,80 @@
+"""Resources of the built quantizer kernels, read from the library's own code object
+metadata (no GPU needed): an input array that lands in scratch memory costs each
+kernel its whole input once more in memory traffic, without any wrong result."""
+import os
+import re
+import struct
+import subprocess
+
+import pytest
+
+READELF = os.path.join(os.environ.get("ROCM_PATH", "/opt/rocm"), "llvm", "bin", "llvm-readelf")
+MAGIC = b"__CLANG_OFFLOAD_BUNDLE__"
+
+
+def code_objects(path):
+    """gfx950 code objects of the offload bundles in a host library."""
+    data = open(path, "rb").read()
+    at = data.find(MAGIC)
+    while at >= 0:
+        n, = struct.unpack_from("<Q", data, at + 24)
+        p = at + 32
+        for _ in range(n):
+            off, size, length = struct.unpack_from("<QQQ", data, p)
+            triple = data[p + 24:p + 24 + length].decode()
+            p += 24 + length
+            if "gfx950" in triple and size:
+                yield data[at + off:at + off + size]
+        at = data.find(MAGIC, at + 24)
+
+
+@pytest.fixture(scope="module")
+def kernels(tmp_path_factory):
+    """Kernel name with its template arguments -> scratch and LDS bytes, VGPRs."""
+    import paper_2607_24953_amd as q2d
+    if not os.path.exists(READELF):
+        pytest.skip("no llvm-readelf")
+    found = {}
+    for i, obj in enumerate(code_objects(q2d.lib_path)):
+        f = tmp_path_factory.mktemp("co") / ("%d.co" % i)
+        f.write_bytes(obj)
+        text = subprocess.run([READELF, "--notes", str(f)], check=True, capture_output=True, text=True).stdout
+        for part in re.split(r"\n  - ", text)[1:]:
+            field = {k: re.search(r"\.%s:\s*'?([\w.]+)" % k, part) for k in
+                     ("symbol", "private_segment_fixed_size", "group_segment_fixed_size", "vgpr_count")}
+            if field["symbol"] is None:
+                continue
+            mangled = field["symbol"].group(1).replace(".kd", "")
+            m = re.search(r"((?:fp4|mxfp8)_quantize_kernel)I((?:[ft]|L[a-z]\d+E)+)E", mangled)
+            if m is None:
+                continue
+            args = re.findall(r"[ft]|L[a-z]\d+E", m.group(2))
+            args = tuple({"f": "float", "t": "bf16"}.get(a) or int(a[2:-1]) for a in args)
+            found[m.group(1), args] = tuple(int(field[k].group(1)) for k in
+                                            ("private_segment_fixed_size", "group_segment_fixed_size", "vgpr_count"))
+    return found
+
+
+def select(kernels, name, **want):
+    """{arguments: (scratch, lds, vgprs)} of the kernels of that name whose arguments match."""
+    fields = {"fp4_quantize_kernel": ("type", "vec", "sr", "wr", "grouped", "wc", "oned", "pair"),
+              "mxfp8_quantize_kernel": ("f32", "vec")}[name]
+    out = {}
+    for (n, args), res in kernels.items():
+        if n != name:
+            continue
+        assert len(args) == len(fields), args
+        got = dict(zip(fields, args))
+        if all(got[k] == v for k, v in want.items()):
+            out[args] = res
+    assert out, (name, want)
+    return out
+
+
+@pytest.mark.parametrize("vec", [1, 2])
+def test_vector_load_quantizers_use_no_scratch(kernels, vec):
+    for args, (scratch, _, _) in {**select(kernels, "fp4_quantize_kernel", vec=vec),
+                                  **select(kernels, "mxfp8_quantize_kernel", vec=vec)}.items():
+        # (the grouped float32 kernels with round to nearest spill at their bound of 128 VGPRs)
+        most = 96 if args[:5] == ("float", vec, 0, 4, 1) else 0
+        assert scratch <= most, (args, scratch)
