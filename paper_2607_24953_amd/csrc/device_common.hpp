@@ -156,42 +156,63 @@ __device__ __forceinline__ uint16_t f_to_bf16_rne(float f)
 // No load is skipped, so that all are in flight together: past the edge they go to
 // the matrix's last row and its last 16-byte piece (ALIGNED: the one that holds the
 // last column) or last 8 columns, and the words are put in place afterwards.
-template <int E, bool ALIGNED, int NV>
+//
+// PACE: pauses of 16 cycles between the rows of interior waves.  The rows of a wide
+// matrix lie a power of two apart more often than not, and eight of them asked for
+// back to back queue on few memory channels.
+template <int E, bool ALIGNED, int PACE, int NV>
 __device__ __forceinline__ void load_sub_block(uint32_t (&v)[8][NV], const uint8_t *p, int64_t pitch, int64_t rows,
                                                int64_t cols)
 {
     static_assert(NV == 2 * E, "8 elements");
     constexpr int NB = E / 2;                   // 16-byte pieces of a row
     const bool edge = __builtin_amdgcn_ballot_w64(rows < 8 || cols < 8) != 0;
-    const uint8_t *q = p;
-    if (edge && !ALIGNED && cols < 8) q += (cols - 8) * E;
+    // Rows step from one to the next by adding the pitch (a 64-bit product for each row
+    // held the loads back: 64 x 64 blocks, whose conversion waits for all of them at a
+    // barrier, 16384 x 12288 bf16 SR 143.0 us, now 134.2).
     const int64_t last = (cols * E - 1) & ~int64_t(15);
+    auto load = [&](auto edge_c) __attribute__((always_inline)) {
+        constexpr bool EDGE = decltype(edge_c)::value;
+        const uint8_t *r = p;
+        if (EDGE && !ALIGNED && cols < 8) r += (cols - 8) * E;
+        if (EDGE && rows < 1) r += (rows - 1) * pitch;
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-        const uint8_t *r = q + (!edge || i < rows ? (int64_t)i * pitch : (rows - 1) * pitch);
+        for (int i = 0; i < 8; ++i) {
 #pragma unroll
-        for (int t = 0; t < NB; ++t) {
-            uint4 x;
-            if constexpr (ALIGNED) {
-                x = load_stream16(r + (!edge || 16 * t <= last ? 16 * t : last));
-            } else if constexpr (E == 4) {
-                x = load_words16(r + 16 * t);
-            } else {
-                // the words that hold the eight bf16 values: four from the word of the
-                // first one on and, if that is its upper half, the one behind them
-                // (16-byte loads at 2-byte addresses run at less than half the rate)
-                const bool odd = (reinterpret_cast<uintptr_t>(r) & 2) != 0;
-                const uint8_t *rw = odd ? r - 2 : r;
-                const uint4 y = load_words16(rw);
-                const uint32_t z = *reinterpret_cast<const uint32_t *>(odd ? rw + 16 : rw + 12);
-                x = odd ? make_uint4((y.x >> 16) | (y.y << 16), (y.y >> 16) | (y.z << 16), (y.z >> 16) | (y.w << 16),
-                                     (y.w >> 16) | (z << 16))
-                        : y;
+            for (int t = 0; t < NB; ++t) {
+                uint4 x;
+                if constexpr (ALIGNED) {
+                    x = load_stream16(r + (!EDGE || 16 * t <= last ? 16 * t : last));
+                } else if constexpr (E == 4) {
+                    x = load_words16(r + 16 * t);
+                } else {
+                    // the words that hold the eight bf16 values: four from the word of the
+                    // first one on and, if that is its upper half, the one behind them
+                    // (16-byte loads at 2-byte addresses run at less than half the rate)
+                    const bool odd = (reinterpret_cast<uintptr_t>(r) & 2) != 0;
+                    const uint8_t *rw = odd ? r - 2 : r;
+                    const uint4 y = load_words16(rw);
+                    const uint32_t z = *reinterpret_cast<const uint32_t *>(odd ? rw + 16 : rw + 12);
+                    x = odd ? make_uint4((y.x >> 16) | (y.y << 16), (y.y >> 16) | (y.z << 16), (y.z >> 16) | (y.w << 16),
+                                         (y.w >> 16) | (z << 16))
+                            : y;
+                }
+                v[i][4 * t] = x.x; v[i][4 * t + 1] = x.y; v[i][4 * t + 2] = x.z; v[i][4 * t + 3] = x.w;
             }
-            v[i][4 * t] = x.x; v[i][4 * t + 1] = x.y; v[i][4 * t + 2] = x.z; v[i][4 * t + 3] = x.w;
+            r += !EDGE || i + 1 < rows ? pitch : 0;
+            if constexpr (PACE > 0 && !EDGE) {
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int n = 0; n < PACE; ++n) asm volatile("s_nop 15");
+                __builtin_amdgcn_sched_barrier(0);
+            }
         }
+    };
+    if (!edge) {
+        load(std::false_type{});
+        return;
     }
-    if (!edge) return;
+    load(std::true_type{});
     const int nr = rows < 8 ? (int)(rows < 0 ? 0 : rows) : 8, nc = cols < 8 ? (int)(cols < 0 ? 0 : cols) : 8;
     if (!ALIGNED) {
         // the lane that holds the last columns read 8 - nc earlier ones before them

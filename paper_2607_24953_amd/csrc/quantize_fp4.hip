@@ -175,6 +175,12 @@ __device__ __forceinline__ void quantize_tile(QuantArgs a, const int64_t tr, con
     constexpr int kThreads = 64 * WR * WC;
     constexpr bool PK = sizeof(T) == 2;     // bf16: two elements per register
     constexpr int NV = PK ? 4 : 8;
+    // pauses between the row loads of a large tensor's tiles (see load_sub_block).  Without
+    // and with them: 196608 x 2048 bf16 RTN 236.9 / 231.7 us, 16384 x 4096 bf16 RTN 39.7 /
+    // 39.1, 8192 x 4096 float32 RTN 41.6 / 41.2, SR 46.5 / 45.1, 1D RTN 47.1 / 43.8.  Better
+    // without: bf16 SR (8192 x 5632 32.2 / 34.7), 1D bf16 (16384 x 4096 40.5 / 41.2) and 1D
+    // float32 SR (8192 x 4096 52.0 / 52.8); strips wait for one tile's latency
+    constexpr int kPace = VEC != 2 || WR != 4 || (ONED && (PK || SR)) ? 0 : PK ? (SR ? 0 : 1) : 3;
     const int lane = threadIdx.x & 63;
     const int wave = threadIdx.x >> 6;
     const int wr = wave / WC, wc = wave % WC;
@@ -188,7 +194,7 @@ __device__ __forceinline__ void quantize_tile(QuantArgs a, const int64_t tr, con
     // columns 2k (low half) and 2k+1 (high half) of row i; fp32: bit patterns.
     uint32_t v[8][NV];
     if constexpr (VEC != 0) {
-        load_sub_block<(int)sizeof(T), VEC == 2>(v, reinterpret_cast<const uint8_t *>(x + r0 * a.stride_r + c0),
+        load_sub_block<(int)sizeof(T), VEC == 2, kPace>(v, reinterpret_cast<const uint8_t *>(x + r0 * a.stride_r + c0),
                                                  a.stride_r * (int64_t)sizeof(T), a.rows - r0, a.cols - c0);
     } else {
 #pragma unroll

@@ -69,7 +69,9 @@ __global__ __launch_bounds__(256) void mxfp8_quantize_kernel(const QuantArgs a)
     uint32_t v[8][NV];
     if constexpr (VEC != 0) {
         constexpr int E = F32 ? 4 : 2;
-        load_sub_block<E, VEC == 2>(v, reinterpret_cast<const uint8_t *>(a.x) + (r0 * a.stride_r + c0) * E, a.stride_r * E,
+        // pauses between the row loads (see load_sub_block): 16384 x 4096 bf16 60.7 us
+        // without, 59.9 with; 8192 x 4096 float32 47.2 / 46.7
+        load_sub_block<E, VEC == 2, VEC != 2 ? 0 : F32 ? 3 : 1>(v, reinterpret_cast<const uint8_t *>(a.x) + (r0 * a.stride_r + c0) * E, a.stride_r * E,
                                     a.rows - r0, a.cols - c0);
     } else {
 #pragma unroll

@@ -8,6 +8,8 @@ import subprocess
 
 import pytest
 
+from launches import kernel_name
+
 READELF = os.path.join(os.environ.get("ROCM_PATH", "/opt/rocm"), "llvm", "bin", "llvm-readelf")
 MAGIC = b"__CLANG_OFFLOAD_BUNDLE__"
 
@@ -44,14 +46,10 @@ def kernels(tmp_path_factory):
                      ("symbol", "private_segment_fixed_size", "group_segment_fixed_size", "vgpr_count")}
             if field["symbol"] is None:
                 continue
-            mangled = field["symbol"].group(1).replace(".kd", "")
-            m = re.search(r"((?:fp4|mxfp8)_quantize_kernel)I((?:[ft]|L[a-z]\d+E)+)E", mangled)
-            if m is None:
-                continue
-            args = re.findall(r"[ft]|L[a-z]\d+E", m.group(2))
-            args = tuple({"f": "float", "t": "bf16"}.get(a) or int(a[2:-1]) for a in args)
-            found[m.group(1), args] = tuple(int(field[k].group(1)) for k in
-                                            ("private_segment_fixed_size", "group_segment_fixed_size", "vgpr_count"))
+            name = kernel_name(field["symbol"].group(1))
+            if name is not None:
+                found[name] = tuple(int(field[k].group(1)) for k in
+                                    ("private_segment_fixed_size", "group_segment_fixed_size", "vgpr_count"))
     return found
 
 
