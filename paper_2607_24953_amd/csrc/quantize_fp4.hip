@@ -646,14 +646,17 @@ hipError_t launch_w(const QuantArgs &a, const QuantArgs *a2, hipStream_t s)
     if (G) nb = nb < 8 * (int64_t)cu_count() ? nb : 8 * (int64_t)cu_count();
     const int64_t all = nb + (a2 ? blocks(*a2) : 0);
     if (all > INT32_MAX) return hipErrorInvalidValue;           // (beyond any device's memory)
-    // an input of 96 MB or more streams from HBM, and two workgroups (16 waves) a CU
-    // read it faster than the three or four that fit: 128.6 against 134 us for 16384 x
-    // 12288 bf16, round to nearest (129.4 against 138, stochastic); below that size
-    // more waves hide more latency (8192 x 5632 SR: 31.5 against 33.8 us).  Unused
-    // dynamic LDS holds the others off.
-    constexpr int kStatic = G ? 42516 : 34368;
+    // An input of 96 MB or more streams from HBM, and two workgroups (16 waves) a CU
+    // read it faster than the three or four that fit: 124.1 against 127.2 us for 16384 x
+    // 12288 bf16, round to nearest (123.0 against 133.4, stochastic); below that size
+    // more waves hide more latency (8192 x 5632 SR: 32.4 against 33.8 us).  Unused
+    // dynamic LDS fills a workgroup's share up to half of the CU's.  The 1D kernels' own
+    // registers already hold them at two (41.5 us for 16384 x 4096 bf16, with or without
+    // the fill).
+    constexpr int kHalf = 81920, kStatic = G ? 42516 : 34368;   // the kernel's own LDS
     auto streams = [](const QuantArgs &q) { return q.rows * q.cols * (int64_t)sizeof(T) >= (int64_t(96) << 20); };
-    const unsigned lds = WR == 4 && (streams(a) || (a2 && streams(*a2))) ? (unsigned)(80000 - kStatic) : 0;
+    const bool two = WR == 4 && !ONED && (streams(a) || (a2 && streams(*a2)));
+    const unsigned lds = two ? (unsigned)(kHalf - kStatic) : 0;
     const dim3 grid((unsigned)all), block(64 * WR * WC);
     if constexpr (!G && !ONED) {
         if (a2) {

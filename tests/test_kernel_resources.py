@@ -8,7 +8,7 @@ import subprocess
 
 import pytest
 
-from launches import kernel_name
+from launches import kernel_name, record
 
 READELF = os.path.join(os.environ.get("ROCM_PATH", "/opt/rocm"), "llvm", "bin", "llvm-readelf")
 MAGIC = b"__CLANG_OFFLOAD_BUNDLE__"
@@ -76,3 +76,20 @@ def test_vector_load_quantizers_use_no_scratch(kernels, vec):
         # (the grouped float32 kernels with round to nearest spill at their bound of 128 VGPRs)
         most = 96 if args[:5] == ("float", vec, 0, 4, 1) else 0
         assert scratch <= most, (args, scratch)
+
+
+STREAMING = [dict(fn="quantize", R=16384, C=4096, sr=sr, block=block, dt=dt, stride_r=pitch)
+             for sr in (0, 1) for block in (32, 64) for dt in ("bf16", "f32") for pitch in (0, 4099)] + \
+            [dict(fn="quantize_1d", R=16384, C=C, sr=sr, dt=dt, stride_r=pitch)
+             for sr in (0, 1) for C, dt, pitch in ((4096, "bf16", 0), (11008, "bf16", 0), (4096, "f32", 0), (4096, "bf16", 4099))] + \
+            [dict(fn="grouped_quantize", S=131072, C=2048, E=128, sr=sr) for sr in (0, 1)] + \
+            [dict(fn="mxfp8", R=16384, C=4096)]
+
+
+def test_streaming_quantizers_fit_two_workgroups(kernels, tmp_path):
+    """Inputs that stream from HBM: two workgroups of every quantizer fit a CU's 160 KB
+    of LDS, own and dynamic together."""
+    for call, launches in zip(STREAMING, record(STREAMING, tmp_path)):
+        for l in launches:
+            own = kernels[l["kernel"], l["args"]][1]
+            assert 2 * (own + l["lds"]) <= 160 * 1024, (call, l, own)
