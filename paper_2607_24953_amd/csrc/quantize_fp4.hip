@@ -652,10 +652,12 @@ hipError_t launch_w(const QuantArgs &a, const QuantArgs *a2, hipStream_t s)
     // more waves hide more latency (8192 x 5632 SR: 32.4 against 33.8 us).  Unused
     // dynamic LDS fills a workgroup's share up to half of the CU's.  The 1D kernels' own
     // registers already hold them at two (41.5 us for 16384 x 4096 bf16, with or without
-    // the fill).
+    // the fill).  64 x 64 blocks rounded stochastically wait for their maximum at a
+    // barrier between the loads and a long conversion, and more workgroups fill that wait:
+    // 16384 x 4096 43.1 us without the fill, 47.8 with it, 16384 x 12288 129.6 / 134.1.
     constexpr int kHalf = 81920, kStatic = G ? 42516 : 34368;   // the kernel's own LDS
     auto streams = [](const QuantArgs &q) { return q.rows * q.cols * (int64_t)sizeof(T) >= (int64_t(96) << 20); };
-    const bool two = WR == 4 && !ONED && (streams(a) || (a2 && streams(*a2)));
+    const bool two = WR == 4 && !ONED && !(SR && a.block == 64) && (streams(a) || (a2 && streams(*a2)));
     const unsigned lds = two ? (unsigned)(kHalf - kStatic) : 0;
     const dim3 grid((unsigned)all), block(64 * WR * WC);
     if constexpr (!G && !ONED) {

@@ -93,3 +93,10 @@ def test_streaming_quantizers_fit_two_workgroups(kernels, tmp_path):
         for l in launches:
             own = kernels[l["kernel"], l["args"]][1]
             assert 2 * (own + l["lds"]) <= 160 * 1024, (call, l, own)
+
+
+def test_stochastic_64_blocks_are_not_held(kernels, tmp_path):
+    """Their maximum is known behind a barrier only: as many workgroups as fit."""
+    calls = [c for c in STREAMING if c["fn"] == "quantize" and c["sr"] == 1 and c["block"] == 64]
+    for call, launches in zip(calls, record(calls, tmp_path)):
+        assert [l["lds"] for l in launches] == [0], call
