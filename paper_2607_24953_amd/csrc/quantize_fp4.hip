@@ -133,15 +133,17 @@ __device__ __forceinline__ void nibble_transpose8(const uint32_t in[8], uint32_t
     }
 }
 
-// Philox4x32-10 block of counter (g, 0, o0, o1), one 32x32->64 multiply per product
-// (v_mad_u64_u32) and one three-input xor per output word.  The offset and the
-// upper counter word are the same for every lane, so one product of each of the
-// first two rounds is scalar: 18 vector products instead of 20.
-__device__ __forceinline__ void philox_block(uint32_t g, uint32_t o0, uint32_t o1, uint32_t k0, uint32_t k1,
+// Philox4x32-10 block of counter (g lo, g hi, o0, o1), one 32x32->64 multiply per
+// product (v_mad_u64_u32) and one three-input xor per output word.  The offset and,
+// unless WIDE, the upper counter word (0) are the same for every lane, so one product
+// of each of the first two rounds is scalar: 18 vector products instead of 20 (WIDE 19).
+template <bool WIDE>
+__device__ __forceinline__ void philox_block(uint64_t g, uint32_t o0, uint32_t o1, uint32_t k0, uint32_t k1,
                                              uint32_t w[4])
 {
-    const uint64_t s0 = (uint64_t)0xCD9E8D57u * o0, p0 = (uint64_t)0xD2511F53u * g;
-    const uint32_t u0 = (uint32_t)(s0 >> 32) ^ k0, u1 = (uint32_t)s0;                 // round 0: words 0 and 1
+    const uint64_t s0 = (uint64_t)0xCD9E8D57u * o0, p0 = (uint64_t)0xD2511F53u * (uint32_t)g;
+    // round 0: words 0 and 1
+    const uint32_t u0 = (uint32_t)(s0 >> 32) ^ k0 ^ (WIDE ? (uint32_t)(g >> 32) : 0u), u1 = (uint32_t)s0;
     const uint32_t v2 = (uint32_t)(p0 >> 32) ^ (o1 ^ k1), v3 = (uint32_t)p0;          // words 2 and 3
     k0 += 0x9E3779B9u; k1 += 0xBB67AE85u;
     const uint64_t s1 = (uint64_t)0xD2511F53u * u0, p1 = (uint64_t)0xCD9E8D57u * v2;
@@ -153,7 +155,7 @@ __device__ __forceinline__ void philox_block(uint32_t g, uint32_t o0, uint32_t o
         const uint64_t q0 = (uint64_t)0xD2511F53u * c0;
         const uint64_t q1 = (uint64_t)0xCD9E8D57u * c2;
         const uint32_t n0 = xor3_uniform((uint32_t)(q1 >> 32), c1, k0);
-        const uint32_t n2 = r == 2 ? (uint32_t)(q0 >> 32) ^ (c3 ^ k1) : xor3_uniform((uint32_t)(q0 >> 32), c3, k1);
+        const uint32_t n2 = r == 2 && !WIDE ? (uint32_t)(q0 >> 32) ^ (c3 ^ k1) : xor3_uniform((uint32_t)(q0 >> 32), c3, k1);
         c0 = n0; c1 = (uint32_t)q1; c2 = n2; c3 = (uint32_t)q0;
     }
     w[0] = c0; w[1] = c1; w[2] = c2; w[3] = c3;
@@ -164,13 +166,17 @@ __device__ __forceinline__ void philox_block(uint32_t g, uint32_t o0, uint32_t o
 // VEC: 0 -- element by element; 1 -- contiguous rows (stride_c == 1) of any pitch and
 // alignment, read as 16-byte windows; 2 -- rows on 16-byte boundaries (with SR, also
 // on storage indices that are multiples of 8).  1 and 2 with SR: every storage
-// index is below 2^35, so the upper Philox counter word is 0.
+// index is below 2^35, so the upper Philox counter word is 0.  3 and 4 (SR only): as 1
+// and 2 with larger indices.
 // SR: stochastic rounding.
 // GROUPED: the rows are expert segments (see QuantArgs).  WR x WC:
 // 32 x 128 strips per tile, one a wave.  ONED: 1 x 32 / 32 x 1 blocks.
-template <typename T, int VEC, bool SR, int WR, bool GROUPED, int WC, bool ONED>
+template <typename T, int VECW, bool SR, int WR, bool GROUPED, int WC, bool ONED>
 __device__ __forceinline__ void quantize_tile(QuantArgs a, const int64_t tr, const int64_t tc)
 {
+    constexpr bool WIDE = VECW > 2;
+    constexpr int VEC = WIDE ? VECW - 2 : VECW;
+    static_assert(SR || !WIDE, "only the draws depend on the storage index");
     constexpr int kTC = 128 * WC, kTile = 32 * WR;
     constexpr int kThreads = 64 * WR * WC;
     constexpr bool PK = sizeof(T) == 2;     // bf16: two elements per register
@@ -367,7 +373,7 @@ __device__ __forceinline__ void quantize_tile(QuantArgs a, const int64_t tr, con
         uint32_t xw[4] = {0, 0, 0, 0};
         if (VEC == 1) {
             const int64_t idx = a.index_base + (r0 + (cc & 7)) * a.stride_r + (c0 - 8 * cc) + 128;
-            philox_block((uint32_t)((uint64_t)idx >> 3), o0, o1, k0, k1, xw);
+            philox_block<WIDE>((uint64_t)idx >> 3, o0, o1, k0, k1, xw);
         }
         // the draws of row i (storage index idx_row of its first element) as
         // seeds r16 << 16
@@ -375,7 +381,7 @@ __device__ __forceinline__ void quantize_tile(QuantArgs a, const int64_t tr, con
             constexpr int i = decltype(ic)::value;
             uint32_t w[8] = {0, 0, 0, 0, 0, 0, 0, 0};
             if (VEC) {
-                philox_block((uint32_t)((uint64_t)idx_row >> 3), o0, o1, k0, k1, w);
+                philox_block<WIDE>((uint64_t)idx_row >> 3, o0, o1, k0, k1, w);
                 if constexpr (VEC == 1) {
 #pragma unroll
                     for (int j = 0; j < 4; ++j) {
@@ -579,7 +585,7 @@ __device__ __forceinline__ void quantize_tile(QuantArgs a, const int64_t tr, con
 // lines end up evicted by the streaming traffic.
 template <typename T, int VEC, bool SR, int WR, bool GROUPED, int WC, bool ONED, bool PAIR>
 __global__ __launch_bounds__(64 * WR * WC)
-__attribute__((amdgpu_waves_per_eu(VEC && SR ? (ONED && VEC == 1 ? 2 : 3) : (VEC ? 4 : 1)))) void fp4_quantize_kernel(QuantArgs a, QuantArgs a2, uint32_t first)
+__attribute__((amdgpu_waves_per_eu(VEC && SR ? (ONED && (VEC & 1) ? 2 : 3) : (VEC ? 4 : 1)))) void fp4_quantize_kernel(QuantArgs a, QuantArgs a2, uint32_t first)
 {
     static_assert(!(ONED && GROUPED), "grouped tensors use 2D blocks");
     static_assert(WR == 4 || (WR == 1 && !ONED && !GROUPED), "a strip of its own: dense 2D blocks of 32");
@@ -660,7 +666,7 @@ hipError_t launch_w(const QuantArgs &a, const QuantArgs *a2, hipStream_t s)
     const bool two = WR == 4 && !ONED && !(SR && a.block == 64) && (streams(a) || (a2 && streams(*a2)));
     const unsigned lds = two ? (unsigned)(kHalf - kStatic) : 0;
     const dim3 grid((unsigned)all), block(64 * WR * WC);
-    if constexpr (!G && !ONED) {
+    if constexpr (!G && !ONED && VEC <= 2) {
         if (a2) {
             hipLaunchKernelGGL((fp4_quantize_kernel<T, VEC, SR, WR, G, WC, ONED, true>), grid, block, lds, s, a, *a2, (uint32_t)nb);
             return hipGetLastError();
@@ -691,6 +697,8 @@ template <typename T, bool G, bool ONED>
 hipError_t launch_dtype(const QuantArgs &a, const QuantArgs *a2, int vec, bool sr, hipStream_t s)
 {
     switch (vec) {
+    case 4: return launch_w<T, 4, true, G, 4, 2, ONED>(a, nullptr, s);
+    case 3: return launch_w<T, 3, true, G, 4, 2, ONED>(a, nullptr, s);
     case 2: return sr ? launch_t<T, 2, true, G, ONED>(a, a2, s) : launch_t<T, 2, false, G, ONED>(a, a2, s);
     case 1: return sr ? launch_t<T, 1, true, G, ONED>(a, a2, s) : launch_t<T, 1, false, G, ONED>(a, a2, s);
     default: return sr ? launch_t<T, 0, true, G, ONED>(a, a2, s) : launch_t<T, 0, false, G, ONED>(a, a2, s);
@@ -698,14 +706,18 @@ hipError_t launch_dtype(const QuantArgs &a, const QuantArgs *a2, int vec, bool s
 }
 
 // How a tensor's rows can be read: contiguous rows of any pitch and alignment take
-// the vector loads (SR up to storage index 2^35, a Philox block past the end
-// included); 2: rows start on 16-byte boundaries and, for SR, on Philox blocks.
+// the vector loads; 2: rows start on 16-byte boundaries and, for SR, on Philox blocks.
+// SR from storage index 2^35 on (a Philox block past the end included) needs the upper
+// counter word: 3 and 4, so that the smaller tensors do not pay for it (4096 x 4096 bf16
+// rows that reach past that index: 15.5 us, element by element 49.4).
 int vec_of(const QuantArgs &a, int dtype_bytes, bool sr)
 {
-    if (a.stride_c != 1 || (sr && a.index_base + a.rows * a.stride_r + a.cols >= (int64_t(1) << 35) - 4096)) return 0;
+    if (a.stride_c != 1) return 0;
     const bool aligned = reinterpret_cast<uintptr_t>(a.x) % 16 == 0 && (a.stride_r * dtype_bytes) % 16 == 0;
     const bool a8 = a.stride_r % 8 == 0 && a.index_base % 8 == 0;
-    return aligned && (a8 || !sr) ? 2 : a.cols >= 8 ? 1 : 0;
+    const int vec = aligned && (a8 || !sr) ? 2 : a.cols >= 8 ? 1 : 0;
+    const bool wide = sr && a.index_base + a.rows * a.stride_r + a.cols >= (int64_t(1) << 35) - 4096;
+    return vec && wide ? vec + 2 : vec;
 }
 
 }  // namespace
@@ -722,7 +734,7 @@ hipError_t launch_fp4_quantize(const QuantArgs &a, int dtype_bytes, bool sr, boo
         QuantArgs one = a;
         one.also = nullptr;
         const int64_t bytes = (a.rows * a.cols + a.also->rows * a.also->cols) * dtype_bytes;
-        if (vec != vec_of(*a.also, dtype_bytes, sr) || bytes > (int64_t(128) << 20)) {
+        if (vec != vec_of(*a.also, dtype_bytes, sr) || vec > 2 || bytes > (int64_t(128) << 20)) {
             const hipError_t e = launch_fp4_quantize(one, dtype_bytes, sr, false, stream);
             return e != hipSuccess ? e : launch_fp4_quantize(*a.also, dtype_bytes, sr, false, stream);
         }
