@@ -110,7 +110,7 @@ def _dtype_code(t: torch.dtype) -> int:
 _BUFFERS = ("codes", "codes_t", "scales", "scales_t")
 
 
-@functools.lru_cache(maxsize=1024)
+@functools.lru_cache(maxsize=1024, typed=True)
 def _layout(fmt: int, rows: int, cols: int, block: int, nseg: int | None, orientations: tuple):
     """Layout of a quantized tensor, from its sizes alone: the descriptor's bytes (no
     buffers), the bytes of the allocation, and name -> (offset, shape) of the
