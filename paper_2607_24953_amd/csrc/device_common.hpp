@@ -208,7 +208,9 @@ __device__ __forceinline__ void load_sub_block(uint32_t (&v)[8][NV], const uint8
             }
         }
     };
-    if (!edge) {
+    // interior waves straight on: between GEMMs a kernel's code is not cached, and a jump
+    // over the edge's loads costs 0.3 us of 15 (4096 x 4096 bf16 1D)
+    if (__builtin_expect(!edge, 1)) {
         load(std::false_type{});
         return;
     }
