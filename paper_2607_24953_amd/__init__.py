@@ -107,14 +107,21 @@ def _dtype_code(t: torch.dtype) -> int:
         raise Q2DError("unsupported dtype %s (float32 or bfloat16)" % t) from None
 
 
-_BUFFERS = ("codes", "codes_t", "scales", "scales_t")
+# the buffers of each orientation
+_BUFFERS = (("codes", "scales"), ("codes_t", "scales_t"))
+
+
+# Up to here one allocation holds both orientations: a step on tensors of this size waits
+# for the host, and a second allocation each costs a layer 2-12 us of 150 (2000 x 2048 x
+# 2048), for at most 4 MiB that are kept along with the other orientation.
+_SHARED_BYTES = 8 << 20
 
 
 @functools.lru_cache(maxsize=1024, typed=True)
 def _layout(fmt: int, rows: int, cols: int, block: int, nseg: int | None, orientations: tuple):
     """Layout of a quantized tensor, from its sizes alone: the descriptor's bytes (no
-    buffers), the bytes of the allocation, and name -> (offset, shape) of the
-    buffers that are wanted, each on a 256-byte boundary."""
+    buffers); the allocations, each with its orientations, its bytes and its buffers'
+    names and offsets (256-byte boundaries); and name -> (offset, shape)."""
     d = _Tensor()
     sizes = (ctypes.c_int64 * 4)()
     if nseg is None:
@@ -124,14 +131,43 @@ def _layout(fmt: int, rows: int, cols: int, block: int, nseg: int | None, orient
             raise Q2DError("grouped tensors are 2D-block FP4 only")
         _check(_lib.q2d_grouped_tensor_init(ctypes.byref(d), rows, cols, nseg, block, sizes),
                "q2d_grouped_tensor_init")
-    wanted = (orientations[0], orientations[1], orientations[0], orientations[1])
-    parts, total = {}, 0
-    for name, size, want in zip(_BUFFERS, sizes, wanted):
-        if want:
+    size = dict(zip(("codes", "codes_t", "scales", "scales_t"), sizes))
+    wanted = [i for i in (0, 1) if orientations[i]]
+    groups = [wanted] if sum(sizes) <= _SHARED_BYTES else [[i] for i in wanted]
+    stores, places = [], {}
+    for group in groups:
+        total = 0
+        names = [name for i in group for name in _BUFFERS[i]]
+        for name in names:
             ld = getattr(d, "ld_" + name)
-            parts[name] = (total, (size // ld, ld))
-            total += (size + 255) // 256 * 256
-    return bytes(d), d.rows, total, parts
+            places[name] = (total, (size[name] // ld, ld))
+            total += (size[name] + 255) // 256 * 256
+        stores.append((tuple(group), total, tuple((n, places[n][0]) for n in names)))
+    return bytes(d), d.rows, tuple(stores), places
+
+
+def _buffer(orientation: int, name: str):
+    def get(self):
+        try:
+            return self._views[name]
+        except KeyError:
+            pass
+        place, t = self._places.get(name), None
+        if place is not None:
+            offset, shape = place
+            t = self._stores[orientation][offset:offset + shape[0] * shape[1]].view(shape)
+        self._views[name] = t
+        return t
+
+    def put(self, value):
+        self._views[name] = value
+        if value is None:
+            # the kernels find no buffer, and the memory goes with the orientation's second
+            setattr(self.desc, name, None)
+            if all(self._views.get(n, self) is None for n in _BUFFERS[orientation]):
+                self._stores[orientation] = None
+
+    return property(get, put, lambda self: put(self, None))
 
 
 class QTensor:
@@ -139,35 +175,34 @@ class QTensor:
 
     ``codes``/``scales`` hold the row-major copy, ``codes_t``/``scales_t`` the
     transposed one; each is a 2-D uint8 tensor of shape (rows, leading dim), or
-    None where that orientation is not wanted.  They are parts of one allocation
-    and are made when first asked for.
+    None where that orientation is not wanted.  They are made when first asked for, as
+    parts of one allocation per orientation (up to 8 MiB, of one for both): keeping or
+    saving one of them keeps or saves that allocation, and setting an orientation's two
+    buffers to None gives its memory back.
 
     With ``nseg`` set it is the padded grouped form of ``rows`` rows cut into
     ``nseg`` segments: ``rows`` is then the padded capacity and
     ``total_rows`` the number of input rows."""
 
+    codes, scales = _buffer(0, "codes"), _buffer(0, "scales")
+    codes_t, scales_t = _buffer(1, "codes_t"), _buffer(1, "scales_t")
+
     def __init__(self, fmt: int, rows: int, cols: int, device, block: int = 32,
                  orientations=(True, True), nseg: int | None = None):
-        template, stored_rows, total, self._parts = _layout(fmt, rows, cols, block, nseg, tuple(orientations))
+        template, stored_rows, stores, self._places = _layout(fmt, rows, cols, block, nseg, tuple(orientations))
         d = self.desc = _Tensor.from_buffer_copy(template)
         self._ref = ctypes.byref(d)
-        self.fmt, self.rows, self.cols, self.device = fmt, stored_rows, cols, torch.device(device)
+        device = torch.device(device)
+        self.fmt, self.rows, self.cols, self.device = fmt, stored_rows, cols, device
         self.total_rows, self.nseg = rows, nseg
-        self._buffer = torch.empty(total, dtype=torch.uint8, device=self.device)
-        base = self._buffer.data_ptr()
-        for name, (offset, _) in self._parts.items():
-            setattr(d, name, base + offset)
-
-    def __getattr__(self, name):
-        if name not in _BUFFERS:
-            raise AttributeError(name)
-        part = self._parts.get(name)
-        t = None
-        if part is not None:
-            offset, shape = part
-            t = self._buffer[offset:offset + shape[0] * shape[1]].view(shape)
-        setattr(self, name, t)
-        return t
+        self._stores, self._views = [None, None], {}
+        for group, total, offsets in stores:
+            t = torch.empty(total, dtype=torch.uint8, device=device)
+            for i in group:
+                self._stores[i] = t
+            base = t.data_ptr()
+            for name, offset in offsets:
+                setattr(d, name, base + offset)
 
     def ptr(self):
         return self._ref
