@@ -217,12 +217,12 @@ def kind_of(kernel_name: str):
     m = re.search(r"gemm_tile_quant_kernel<\d+, \d+, (\w+)>", kernel_name)
     if m:
         return "gemm_fp4_dxq" if m.group(1) == "true" else "gemm_fp4_yq"
-    m = re.search(r"gemm_(?:tile_|ksplit_)?kernel<(\d)", kernel_name)
+    m = re.search(r"gemm_(?:tile|ksplit)_kernel<(\d)", kernel_name)
     if m:
         return "gemm_fp4" if m.group(1) == "0" else "gemm_fp8"
     m = re.search(r"fp4_quantize_kernel<([^>]*)>", kernel_name)
     if m:
-        # template arguments: element type, VEC, SR, row waves, GROUPED, column waves, 1D
+        # template arguments: element type, VEC, SR, row waves, GROUPED, column waves, 1D, two tensors
         a = [t.strip() for t in m.group(1).split(",")]
         if a[6] == "true":
             return "quant_fp4_1d"

@@ -16,25 +16,37 @@ P = "void q2d::(anonymous namespace)::"
 
 
 @pytest.mark.parametrize("name,kind", [
-    (P + "gemm_fp4_persistent_kernel<true, false, 0, 0, false>(q2d::GemmArgs, int, int, q2d::GroupedArgs)", "gemm_fp4"),
-    (P + "gemm_fp4_persistent_kernel<false, true, 0, 3, false>(q2d::GemmArgs, int, int, q2d::GroupedArgs)", "gemm_fp4"),
-    (P + "gemm_fp4_persistent_kernel<true, false, 1, 0, false>(q2d::GemmArgs, int, int, q2d::GroupedArgs)",
+    (P + "gemm_fp4_persistent_kernel<true, false, 0, 0, false, false>(q2d::GemmArgs, int, int, q2d::GroupedArgs)", "gemm_fp4"),
+    (P + "gemm_fp4_persistent_kernel<false, true, 0, 3, false, false>(q2d::GemmArgs, int, int, q2d::GroupedArgs)", "gemm_fp4"),
+    (P + "gemm_fp4_persistent_kernel<true, false, 1, 0, false, false>(q2d::GemmArgs, int, int, q2d::GroupedArgs)",
      "gemm_fp4_grouped"),
-    (P + "gemm_fp4_persistent_kernel<false, false, 2, 0, false>(q2d::GemmArgs, int, int, q2d::GroupedArgs)",
+    (P + "gemm_fp4_persistent_kernel<false, false, 2, 0, false, false>(q2d::GemmArgs, int, int, q2d::GroupedArgs)",
      "gemm_fp4_grouped_k"),
-    (P + "gemm_fp4_persistent_kernel<false, false, 0, 1, true>(q2d::GemmArgs, int, int, q2d::GroupedArgs)",
+    (P + "gemm_fp4_persistent_kernel<false, false, 0, 1, true, false>(q2d::GemmArgs, int, int, q2d::GroupedArgs)",
      "gemm_fp4_yq"),
     (P + "gemm_fp4_persistent_kernel<false, false, 0, 0, true, false>(q2d::GemmArgs, int, int, q2d::GroupedArgs)",
      "gemm_fp4_yq"),
     (P + "gemm_fp4_persistent_kernel<false, false, 0, 0, true, true>(q2d::GemmArgs, int, int, q2d::GroupedArgs)",
      "gemm_fp4_dxq"),
-    (P + "gemm_fp8_256_kernel<true, false>(q2d::GemmArgs, int, int)", "gemm_fp8"),
-    (P + "gemm_kernel<0, true>(q2d::GemmArgs, long, long)", "gemm_fp4"),
-    (P + "gemm_kernel<1, false>(q2d::GemmArgs, long, long)", "gemm_fp8"),
-    (P + "fp4_quantize_kernel<unsigned short, true, false, true, false, 2, false>(q2d::QuantArgs)", "quant_fp4"),
-    (P + "fp4_quantize_kernel<float, true, true, true, true, 1, false>(q2d::QuantArgs)", "quant_fp4_grouped"),
-    (P + "fp4_quantize_kernel<unsigned short, true, false, true, false, 2, true>(q2d::QuantArgs)", "quant_fp4_1d"),
-    (P + "mxfp8_quantize_kernel<false, true>(q2d::QuantArgs)", "quant_mxfp8"),
+    (P + "gemm_fp8_256_kernel<true, false, true>(q2d::GemmArgs, int, int)", "gemm_fp8"),
+    (P + "gemm_ksplit_kernel<0, 1, 1, true, true>(q2d::(anonymous namespace)::Pair)", "gemm_fp4"),
+    (P + "gemm_ksplit_kernel<1, 2, 2, false, false>(q2d::(anonymous namespace)::Pair)", "gemm_fp8"),
+    (P + "gemm_tile_kernel<0, 2, 2, 3, 1, true, false>(q2d::(anonymous namespace)::Pair)", "gemm_fp4"),
+    (P + "gemm_tile_kernel<1, 2, 2, 2, 1, true, true>(q2d::(anonymous namespace)::Pair)", "gemm_fp8"),
+    (P + "gemm_tile_grouped_kernel<true>(q2d::GemmArgs, q2d::GroupedArgs, unsigned int)", "gemm_fp4_grouped"),
+    (P + "gemm_tile_quant_kernel<2, 1, false>(q2d::GemmArgs, unsigned int, unsigned int)", "gemm_fp4_yq"),
+    (P + "gemm_tile_quant_kernel<3, 0, true>(q2d::GemmArgs, unsigned int, unsigned int)", "gemm_fp4_dxq"),
+    (P + "fp4_quantize_kernel<unsigned short, 2, false, 4, false, 2, false, false>(q2d::QuantArgs, q2d::QuantArgs, unsigned int)",
+     "quant_fp4"),
+    (P + "fp4_quantize_kernel<float, 1, true, 1, false, 1, false, true>(q2d::QuantArgs, q2d::QuantArgs, unsigned int)",
+     "quant_fp4"),
+    (P + "fp4_quantize_kernel<float, 2, true, 4, true, 2, false, false>(q2d::QuantArgs, q2d::QuantArgs, unsigned int)",
+     "quant_fp4_grouped"),
+    (P + "fp4_quantize_kernel<unsigned short, 4, true, 4, false, 2, true, false>(q2d::QuantArgs, q2d::QuantArgs, unsigned int)",
+     "quant_fp4_1d"),
+    (P + "mxfp8_quantize_kernel<false, 2>(q2d::QuantArgs)", "quant_mxfp8"),
+    # (not one of the library's)
+    ("gemm_kernel<0, true>(int)", None),
     ("void at::native::vectorized_elementwise_kernel<4, at::native::FillFunctor<float>>(int, float, float)", None),
 ])
 def test_kind_of(name, kind):
