@@ -9,7 +9,7 @@ non-finite value in one 32 x 32 quarter of a block, and full-size 7B-class
 tensors.
 
 GEMMs: block-64 operands, alone and mixed with block-32 and 1D ones, on the
-small-problem and the persistent kernel, and the linear layer with 64 x 64
+K-split and the 128 x 128 tiles, and the linear layer with 64 x 64
 blocks, against the float64 oracle GEMM (relative Frobenius error <= 1e-5 for
 float32 output).
 """
@@ -110,7 +110,7 @@ def _quant(q2d, x, fmt, mode, seed=0, offset=0):
 
 
 GEMM_CASES = [
-    # (M, N, K, ta, tb, fmt_a, fmt_b) on the small kernel and the persistent kernel
+    # (M, N, K, ta, tb, fmt_a, fmt_b): K-split tiles, then 128 x 128 ones
     (300, 200, 160, 0, 0, "fp4_64", "fp4_64"),
     (257, 129, 96, 1, 1, "fp4_64", "fp4"),
     (128, 256, 256, 0, 1, "fp4_1d", "fp4_64"),

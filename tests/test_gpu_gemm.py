@@ -40,8 +40,8 @@ def quant(q2d, x, mode, seed=0, offset=0):
 
 GEMM_SHAPES = [(128, 256, 256), (300, 200, 160), (257, 129, 96), (1, 1, 32), (64, 640, 1000),
                (1000, 300, 2000), (384, 512, 4096),
-               # enough 256 x 256 output tiles for the large-tile kernel: ragged M and N,
-               # K shorter than its LDS pipeline (128, 384) and long (2048)
+               # several rounds of 128 x 128 tiles, two workgroups a CU: ragged M and N, K
+               # shorter than the LDS ring (128), one unit longer (384) and long (2048)
                (2048, 4096, 128), (2100, 4000, 384), (4096, 2048, 2048)]
 
 
@@ -61,10 +61,9 @@ def test_gemm_fp4(q2d, M, N, K, ta, tb):
     check_bf16(c16, ref)
 
 
-# More output tiles than the device has CUs, so every workgroup of the
-# persistent kernel walks several tiles; K of 1, 3 and 5 K-tiles (fewer than,
-# and more than, the LDS ring's four stages, so one tile's loads run into the
-# next tile's) and ragged M and N edges.
+# More output tiles than the device has CUs (1089 to 1128 of 128 x 128), K of 1, 3
+# and 5 units of 128, ragged M and N edges.  (The persistent kernel's walk over
+# several tiles: test_gpu_gemm_large.py.)
 MULTI_TILE_SHAPES = [(4200, 4100, 128), (4100, 4200, 384), (6000, 3000, 640)]
 
 
@@ -87,14 +86,14 @@ def test_gemm_fp4_multi_tile_per_workgroup(q2d, M, N, K, ta, tb):
     check_bf16(c16, ref + c0.float().cpu().numpy().astype(np.float64))
 
 
-# bf16 output of the persistent kernel into views of a wider buffer: an even
+# bf16 output of 128 x 128 tiles into views of a wider buffer: an even
 # row pitch (whole-line pair stores), an odd one and a base one element off
 # (both one store per element), with and without accumulation; N is odd, so the
 # last column of every row is a lone element.  Nothing outside the view changes.
 @pytest.mark.parametrize("pad,base", [(6, 0), (1, 0), (2, 1)])
 @pytest.mark.parametrize("acc", [False, True])
 def test_gemm_bf16_strided_output(q2d, pad, base, acc):
-    M, N, K = 2100, 4001, 384                       # 9 x 16 output tiles of 256 x 256
+    M, N, K = 2100, 4001, 384                       # 17 x 32 output tiles of 128 x 128
     A = synth.normal((M, K), 1.0, 31, torch.bfloat16, device=DEV)
     B = synth.normal((N, K), 0.02, 32, torch.bfloat16, device=DEV)
     qa, oa = quant(q2d, A, "rtn")
@@ -114,11 +113,11 @@ def test_gemm_bf16_strided_output(q2d, pad, base, acc):
 
 @pytest.mark.parametrize("pad,base", [(1, 0), (2, 1)])
 def test_gemm_mxfp8_bf16_strided_output(q2d, pad, base):
-    """The large-tile MXFP8 kernel's bf16 output into a view of a wider buffer with
+    """MXFP8 bf16 output of 128 x 128 tiles into a view of a wider buffer with
     an odd row pitch or a base one element off (one store per element) equals,
     byte for byte, the same GEMM written contiguously (pair stores), with and
     without accumulation; the bytes outside the view are unchanged."""
-    M, N, K = 2100, 4001, 512                       # 9 x 16 output tiles of 256 x 256
+    M, N, K = 2100, 4001, 512                       # 17 x 32 output tiles of 128 x 128
     A = synth.normal((M, K), 1.0, 41, torch.bfloat16, device=DEV)
     B = synth.normal((N, K), 0.02, 42, torch.bfloat16, device=DEV)
     qa, qb = q2d.mxfp8_quantize(A), q2d.mxfp8_quantize(B)
@@ -139,10 +138,10 @@ def test_gemm_mxfp8_bf16_strided_output(q2d, pad, base):
 
 
 def test_gemm_deterministic(q2d):
-    """Two runs of each persistent-kernel GEMM (forward with bf16 output, weight
+    """Two runs of each GEMM of 128 x 128 tiles (forward with bf16 output, weight
     gradient with fp32 output, the quantizing epilogue) on the same operands give
     identical bytes: no atomics, a fixed reduction order per output element."""
-    T, N, K = 2048, 4096, 1024                      # 128 output tiles of 256 x 256
+    T, N, K = 2048, 4096, 1024                      # 512 output tiles of 128 x 128 in the forward
     X = synth.normal((T, K), 1.0, 611, torch.bfloat16, device=DEV)
     W = synth.normal((N, K), 0.02, 612, torch.bfloat16, device=DEV)
     dY = synth.normal((T, N), 1e-3, 613, torch.bfloat16, device=DEV)
@@ -195,8 +194,8 @@ def test_gemm_unit_scales_exact(q2d):
 @pytest.mark.parametrize("M,N,K,ta,tb", [(300, 200, 160, 0, 0), (2100, 4000, 384, 0, 1), (4096, 2048, 640, 1, 1)])
 def test_gemm_non_finite_blocks(q2d, M, N, K, ta, tb):
     """A NaN and an infinity in two blocks of A give those blocks scale 0xFF (NaN):
-    exactly the output entries whose dot product meets them are NaN, on the small and
-    the persistent kernel, and the rest match the oracle."""
+    exactly the output entries whose dot product meets them are NaN, on the K-split and
+    the 128 x 128 tiles, and the rest match the oracle."""
     A = synth.normal((K, M) if ta else (M, K), 1.0, 91, torch.float32)
     B = synth.normal((K, N) if tb else (N, K), 0.02, 92, torch.float32)
     A[5, 7] = float("nan")
@@ -234,11 +233,8 @@ def test_linear_fwd_bwd(q2d, T, N, K):
 
 
 @pytest.mark.parametrize("M,N,K", [(128, 256, 256), (300, 200, 160), (1000, 300, 2000),
-                                   # enough 256 x 256 tiles for the large-tile kernel: ragged
-                                   # edges, K shorter than its 4-stage ring (256 = 4 K-tiles of 64);
-                                   # 16-byte scale groups of 8 K-tiles for K = 1024 and 1536 (an
-                                   # odd number of groups), per-word scales for K = 640 and 256
-                                   # (not multiples of 512)
+                                   # 128 x 128 tiles, two workgroups a CU, with ragged edges, and
+                                   # (4096 x 2304, K of three scale groups) the 256 x 256 kernel
                                    (4096, 2048, 1024), (4096, 2304, 1536), (4000, 2100, 640),
                                    (2048, 4224, 256)])
 @pytest.mark.parametrize("ta,tb", [(0, 0), (0, 1), (1, 1), (1, 0)])

@@ -4,7 +4,7 @@ in the epilogue; App. C) against the oracle.
 * Exact cases: operands on the E2M1 grid with a 6 in every block (unit
   scales) make the float32 accumulation exact, so every byte of the four
   output buffers must equal the oracle's quantization of the exact product:
-  ragged shapes on one and several 256 x 256 tiles, all transpose flags, 1D
+  ragged shapes on one and several 128 x 128 tiles, all transpose flags, 1D
   operands, a result that overflows float32 (scale 0xFF, zero codes).
 * General cases (normal inputs, mixed scales): the float32 accumulation may
   move a value across a rounding boundary, so the check is that the result is

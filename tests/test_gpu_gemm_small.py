@@ -1,6 +1,6 @@
 """GPU parity of the small-tile GEMM kernels against the float64 oracle, at the
 sizes where they can go wrong: one and several tiles of every kind with ragged
-M and N (clamped operand rows, masked stores), K of 1 to 14 units of 128 (shorter
+M and N (clamped operand rows, masked stores), K of 1 to 32 units of 128 (shorter
 than, equal to and longer than the LDS rings; odd numbers of units, where the last
 128-byte stage is half empty), one to four waves with work in the K-split kernel.
 
@@ -23,7 +23,9 @@ DEV = "cuda:0"
 SHAPES = [(1, 1, 1), (33, 31, 65), (100, 290, 640), (16, 260, 1700), (31, 700, 300),
           (500, 600, 1300), (250, 1000, 1792), (256, 2048, 4096),
           (700, 1100, 1300), (900, 1030, 1792), (1003, 1111, 1999),
-          (2100, 2050, 700), (1800, 3000, 1700)]
+          (2100, 2050, 700), (1800, 3000, 1700),
+          # odd numbers of units on both rings of the 128 x 128 tiles, one to three units
+          (1003, 1111, 1900), (1500, 1600, 300), (520, 4100, 100), (2100, 2050, 100), (2100, 2050, 370), (1800, 3000, 1650)]
 
 
 @pytest.fixture(scope="module")

@@ -8,7 +8,7 @@ blocks, every finite bfloat16 value under every block exponent it can meet,
 float32 midpoints and subnormals, and the 7B-class activation at full size.
 
 GEMMs: 1D operands mixed with 2D ones (forward: A = X rowwise; weight
-gradient: B = X colwise) on the small-problem and the persistent kernel, and
+gradient: B = X colwise) on the K-split and the 128 x 128 tiles, and
 the linear layer with 1D activations, against the float64 oracle GEMM
 (relative Frobenius error <= 1e-5 for float32 output).
 """
@@ -150,7 +150,7 @@ def _quant(q2d, x, fmt, mode, seed=0, offset=0):
 
 GEMM_CASES = [
     # (M, N, K, ta, tb, fmt_a, fmt_b): forward (A = X rowwise 1D), weight gradient
-    # (B = X colwise 1D), both 1D, on the small kernel and the persistent kernel
+    # (B = X colwise 1D), both 1D: K-split tiles, then 128 x 128 ones
     (300, 200, 160, 0, 0, "fp4_1d", "fp4"),
     (257, 129, 96, 1, 1, "fp4", "fp4_1d"),
     (128, 256, 256, 0, 0, "fp4_1d", "fp4_1d"),
@@ -170,8 +170,8 @@ def test_gemm_with_1d_operands(q2d, M, N, K, ta, tb, fa, fb):
     ref = oracle.gemm(oracle.operand(oa, bool(ta), fa), oracle.operand(ob, bool(tb), fb))
     c32 = q2d.q2d_gemm(qa, ta, qb, tb, out_dtype=torch.float32)
     assert rel_frob(c32.cpu().numpy(), ref) <= TOL
-    # bf16 output: on the persistent kernel, interleaved output columns (a 1D B
-    # operand's row words follow its permuted rows)
+    # bf16 output: interleaved output columns (a 1D B operand's row words follow its
+    # permuted rows)
     check_bf16(q2d.q2d_gemm(qa, ta, qb, tb, out_dtype=torch.bfloat16), ref)
 
 
