@@ -186,11 +186,11 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &g, uint8_t *smem, uint
     constexpr int TM = 64 * TI, TN = 64 * TJ, kRows = TM + TN;
     constexpr int kWords = 128 * kRows;                         // byte offset of the scale words in a stage
     constexpr int WU = F8 ? 1 : 2;                              // scale words per row and stage
-    constexpr int WG = WM ? (kRows / 64 + 3) / 4 : 1;           // 64-row word groups per wave
     constexpr int kStage = kWords + (WM ? 4 * WU * kRows : 4 * 256);
-    constexpr int CODES = kRows / 32, WORDS = WM ? WU * WG : 1; // this wave's loads per stage
+    constexpr int CODES = kRows / 32, WORDS = WM ? WU : 1;      // this wave's loads per stage
     constexpr int LOADS = CODES + WORDS, H1 = (LOADS + 1) / 2;  // the first H1 in the second unit
     static_assert(WM || !F8, "MXFP8 has one word per row");
+    static_assert(kRows == 256, "each wave loads the words of 64 rows");
     static_assert(RING * kStage == tile_lds_bytes<FMT, TI, TJ, RING, WM>(), "the caller's LDS");
 
     const int64_t m0 = (int64_t)tm * TM, n0 = (int64_t)tn * TN;
@@ -206,7 +206,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &g, uint8_t *smem, uint
         const int64_t lim = t < TM ? g.M : g.N;
         return r < lim ? r : lim - 1;
     };
-    const uint8_t *pc[CODES], *pw[WORDS];
+    const uint8_t *pc[CODES], *pw;
 #pragma unroll
     for (int k = 0; k < CODES; ++k) {
         const int t = 32 * k + 8 * wave + (lane >> 3), c16 = ((lane & 7) ^ swz128(t)) * 16;
@@ -215,8 +215,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &g, uint8_t *smem, uint
     // the last stage of an odd number of units: its second half does not exist (rows
     // t and t + 32 k have the same swizzle, so this holds for every load)
     const int back = ((lane & 7) ^ swz128(8 * wave + (lane >> 3))) >= 4 ? 64 : 0;
-    int64_t wstep[WG];                                          // bytes per unit (MXFP8: per stage)
-    int wgrp[WG];
+    int64_t wstep = 4;                                          // bytes per unit (MXFP8: per stage)
     if constexpr (WM == 0) {
         // lane: unit lane / 32, block row lane % 32 of the wave's TI + TJ (clamped)
         const int x = (lane & 31) < TI + TJ ? (lane & 31) : TI + TJ - 1;
@@ -224,19 +223,14 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &g, uint8_t *smem, uint
         int64_t r = is_a ? m0 + wm * 32 * TI + 32 * x : n0 + wn * 32 * TJ + 32 * (x - TI);
         const int64_t lim = is_a ? g.M : g.N;
         r = r < lim ? r : lim - 1;
-        pw[0] = (is_a ? g.sa : g.sb) + (r >> 5) * (is_a ? g.ldsa : g.ldsb) + 4 * half;
-        wgrp[0] = wave; wstep[0] = 4;
+        pw = (is_a ? g.sa : g.sb) + (r >> 5) * (is_a ? g.ldsa : g.ldsb) + 4 * half;
     } else {
-        // 64-row groups wave, 4 + wave % 2; a group belongs to one operand
-#pragma unroll
-        for (int k = 0; k < WG; ++k) {
-            wgrp[k] = k == 0 ? wave : 4 + (wave & 1);
-            const bool is_a = wgrp[k] < TI;
-            const bool oned = is_a ? g.a1d : g.b1d;
-            const int64_t ld = is_a ? g.ldsa : g.ldsb;
-            wstep[k] = !F8 && oned ? ld : 4;
-            pw[k] = (is_a ? g.sa : g.sb) + word_row<FMT>(row_of(64 * wgrp[k] + lane), ld, oned);
-        }
+        // rows 64 wave + lane, of one operand
+        const bool is_a = wave < TI;
+        const bool oned = is_a ? g.a1d : g.b1d;
+        const int64_t ld = is_a ? g.ldsa : g.ldsb;
+        if (!F8 && oned) wstep = ld;
+        pw = (is_a ? g.sa : g.sb) + word_row<FMT>(row_of(64 * wave + lane), ld, oned);
     }
     const uint32_t lds0 = (uint32_t)(uintptr_t)&smem[0];
     // load k of stage s: codes, then scale words (past the last stage: that one
@@ -249,12 +243,12 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &g, uint8_t *smem, uint
             const uint8_t *p = pc[k < CODES ? k : 0] + (uint64_t)t * 128;
             lds_dma16(cut ? p - back : p, stage + (4 * k + wave) * 1024);
         } else if (WM == 0) {
-            const uint8_t *p = pw[0] + (uint64_t)t * 8;
+            const uint8_t *p = pw + (uint64_t)t * 8;
             lds_dma4(cut && half ? p - 4 : p, stage + kWords + wave * 256);
         } else {
-            const int w = k < CODES ? 0 : k - CODES, u = w / WG, gi = w % WG;
+            const int u = k - CODES;
             const uint32_t ut = F8 ? t : (cut ? 2 * t : 2 * t + u);
-            lds_dma4(pw[gi] + ut * wstep[gi], stage + kWords + u * (4 * kRows) + wgrp[gi] * 256);
+            lds_dma4(pw + ut * wstep, stage + kWords + u * (4 * kRows) + wave * 256);
         }
     };
 
