@@ -367,10 +367,11 @@ q2d_status q2d_linear_fwd(const void *X, const void *W, q2d_dtype dt, int64_t T,
 {
     if (!qX || !qW || !qX->codes || !qW->codes) return Q2D_EINVAL;
     // every step is checked (go = false) before the first one is launched; two 2D
-    // quantizations with the same rounding go out together
+    // quantizations with the same rounding go out together, unless W's replaces X's
     QuantArgs ax, aw;
     const bool oned = qX->fmt == Q2D_FMT_FP4_1D;
-    const bool both = !oned && ((int)mode_x & ~Q2D_FLOOR_SCALE) == ((int)mode_w & ~Q2D_FLOOR_SCALE);
+    const bool shared = qX->codes == qW->codes || (qX->codes_t && qX->codes_t == qW->codes_t);
+    const bool both = !oned && !shared && ((int)mode_x & ~Q2D_FLOOR_SCALE) == ((int)mode_w & ~Q2D_FLOOR_SCALE);
     for (const bool go : {false, true}) {
         if (go && both) {
             ax.also = &aw;
@@ -397,7 +398,7 @@ q2d_status q2d_linear_bwd(const void *dY, q2d_dtype dt, const q2d_tensor *qX, co
     if (qW->cols != K || qdY->rows != T || qdY->cols != N) return Q2D_EINVAL;
     if (!qdY->codes || !qdY->codes_t || !qX->codes_t || !qW->codes_t) return Q2D_EINVAL;
     // every step is checked before the first one is launched; the two products go out
-    // together
+    // together, unless the second one's result falls on the first one's
     for (const bool go : {false, true}) {
         GemmArgs gx, gw;
         q2d_status s = quantize_impl(dY, dt, T, N, N, 1, qdY->block, mode_dy, seed, offset_dy, qdY, stream, go);
@@ -405,6 +406,15 @@ q2d_status q2d_linear_bwd(const void *dY, q2d_dtype dt, const q2d_tensor *qX, co
         if (s == Q2D_OK) s = gemm_impl(qdY, 1, qX, 1, dW, dw_dt, K, accumulate_dw, stream, false, &gw);
         if (s != Q2D_OK) return s;
         if (!go) continue;
+        const uint64_t x0 = reinterpret_cast<uintptr_t>(dX), w0 = reinterpret_cast<uintptr_t>(dW);
+        const uint64_t x1 = x0 + (uint64_t)T * (uint64_t)K * dtype_bytes(dx_dt);
+        const uint64_t w1 = w0 + (uint64_t)N * (uint64_t)K * dtype_bytes(dw_dt);
+        if (x0 < w1 && w0 < x1) {
+            if (launch_gemm(gx, kFmtFp4Block2D, dx_dt == Q2D_BF16, stream) != hipSuccess ||
+                launch_gemm(gw, kFmtFp4Block2D, dw_dt == Q2D_BF16, stream) != hipSuccess)
+                return Q2D_ELAUNCH;
+            continue;
+        }
         gx.also = &gw;
         gx.also_bf16 = dw_dt == Q2D_BF16;
         // (the formats are FP4: quantize_impl has checked dY's, and operands pair only so)

@@ -9,7 +9,8 @@ entry point in "fn" and the sizes it takes:
   gemm                              M N K ta tb fmt c_dt [ldc] [c] [acc]
   gemm_quantized                    M N K ta tb fmt [sr]
   grouped_gemm                      S N K E ta tb c_dt [ldc]
-  linear_fwd, linear_bwd            T N K dt [oned] [block]
+  linear_fwd, linear_bwd            T N K dt [oned] [block]; same: one descriptor for X and W,
+                                    one buffer for dX and dW
 fmt: "2d", "mxfp8", or which operands have 1D blocks ("a1", "b1", "a1b1").
 dt, c_dt: "f32" or "bf16".  x, c: the address (its alignment matters).
 A launch is a dict: kernel, args (its template arguments), grid, block, lds (dynamic)."""
@@ -88,7 +89,7 @@ def _main(so):
         return tensor(f, cols, rows) if trans else tensor(f, rows, cols)
 
     def call(fn, dt="bf16", sr=0, block=32, x=BASE, c=BASE, acc=0, c_dt="bf16", ldc=0, ta=0, tb=0, fmt="2d", R=0, C=0,
-             S=0, E=0, T=0, M=0, N=0, K=0, stride_r=0, oned=0):
+             S=0, E=0, T=0, M=0, N=0, K=0, stride_r=0, oned=0, same=0):
         d, s = DT[dt], U64(1)
         if fn in ("quantize", "quantize_1d"):
             out = tensor(FP4_1D if fn == "quantize_1d" else FP4_2D, R, C, block)
@@ -108,10 +109,14 @@ def _main(so):
             b = tensor(FP4_2D, S, N, 32, E) if ta else tensor(FP4_2D, E * K, N) if tb else tensor(FP4_2D, E * N, K)
             return lib.q2d_grouped_gemm(a, ta, b, tb, E, P(BASE * 6), I64(S), P(c), DT[c_dt], I64(ldc or N), acc, None)
         qx, qw = tensor(FP4_1D if oned else FP4_2D, T, K, 32 if oned else block), tensor(FP4_2D, N, K, block)
+        if not same:
+            for k in ("codes", "codes_t", "scales", "scales_t"):
+                setattr(qw._obj, k, getattr(qw._obj, k) + BASE // 2)
         if fn == "linear_fwd":
             return lib.q2d_linear_fwd(P(x), P(BASE * 7), d, I64(T), I64(N), I64(K), sr, sr, s, s, s, qx, qw, P(c), d, None)
         assert fn == "linear_bwd", fn
-        return lib.q2d_linear_bwd(P(x), d, qx, qw, 1, s, s, tensor(FP4_2D, T, N, block), P(c), d, P(BASE * 8), 0, acc, None)
+        return lib.q2d_linear_bwd(P(x), d, qx, qw, 1, s, s, tensor(FP4_2D, T, N, block), P(c), d,
+                                  P(c if same else BASE * 8), d, acc, None)
 
     out = []
     for kw in json.load(sys.stdin):

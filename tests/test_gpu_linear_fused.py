@@ -2,7 +2,7 @@
 grid of small tiles) give what the separate calls give, byte for byte: tensors of
 one and of several workgroup shapes, a ragged and an odd width (rows read in
 different ways), mixed rounding, 64 x 64 blocks beside 32 x 32 ones, output types in
-every combination, and an accumulated dW."""
+every combination, and an accumulated dW; results that share memory keep their order."""
 import pytest
 import torch
 
@@ -51,3 +51,23 @@ def test_linear_equals_separate_calls(q2d, T, N, K, dtype, mx, mw, fmt1d, bx, bw
             assert torch.equal(acc, 2 * want)           # the same sums again, and doubling is exact
         else:
             assert torch.allclose(acc.float(), 2 * want.float(), rtol=2.0 ** -7, atol=0)
+
+
+def test_results_in_one_buffer(q2d):
+    """One descriptor for X and W (the second quantization stays), one buffer for dX and an
+    accumulated dW (their sum): as from the calls one after the other."""
+    n = 256
+    X, W = (synth.normal((n, n), 1.0, k, torch.float32, device=DEV) for k in (1, 2))
+    q = q2d.QTensor(q2d.FP4_2D, n, n, DEV)
+    Y, _, _ = q2d.q2d_linear_fwd(X, W, "sr", "sr", 7, 3, 4, y_dtype=torch.float32, qX=q, qW=q)
+    sW = q2d.q2d_quantize(W, "sr", 7, 4)
+    for k in ("codes", "codes_t", "scales", "scales_t"):
+        assert torch.equal(getattr(q, k), getattr(sW, k)), k
+    assert torch.equal(Y, q2d.q2d_gemm(sW, 0, sW, 0))
+    dY = synth.normal((n, n), 1e-3, 5, torch.float32, device=DEV)
+    sX, sdY = q2d.q2d_quantize(X, "sr", 7, 3), q2d.q2d_quantize(dY, "sr", 7, 5)
+    out = torch.empty((n, n), device=DEV)
+    q2d.q2d_linear_bwd(dY, sX, sW, "sr", 7, 5, dx_dtype=torch.float32, dX=out, dW=out, accumulate_dw=True)
+    want = q2d.q2d_gemm(sdY, 0, sW, 1)
+    q2d.q2d_gemm(sdY, 1, sX, 1, out=want, accumulate=True)
+    assert torch.equal(out, want)

@@ -67,3 +67,12 @@ def test_small_shapes_cover_every_small_tile(tmp_path, fmt):
     tiles = [("gemm_ksplit_kernel", (1, 1)), ("gemm_ksplit_kernel", (2, 2)), ("gemm_tile_kernel", (2, 2, 3)),
              ("gemm_tile_kernel", (2, 2, 2))]
     assert seen >= {(*t, odd) for t in tiles for odd in (0, 1)}, seen
+
+
+def test_shared_launches_keep_the_order_of_overlapping_results(tmp_path):
+    """One descriptor for X and W, one buffer for dX and dW: the second result replaces or
+    adds to the first one's, so each goes out on its own."""
+    calls = [dict(fn=fn, T=256, N=256, K=384, dt="f32", sr=1, same=same, acc=acc)
+             for fn, acc in (("linear_fwd", 0), ("linear_bwd", 0), ("linear_bwd", 1)) for same in (0, 1)]
+    calls = [{k: v for k, v in c.items() if k != "acc" or c["fn"] == "linear_bwd"} for c in calls]
+    assert [len(launches) for launches in record(calls, tmp_path)] == [2, 3, 2, 3, 2, 3]
