@@ -577,15 +577,15 @@ __device__ __forceinline__ void quantize_tile(QuantArgs a, const int64_t tr, con
 }
 
 // A lane holds its 8 x 8 sub-block (32 registers of bf16 pairs, 64 of float32)
-// and converts each element once, so the aligned bf16 variants take 43-50 VGPRs
-// (grouped 67-75) with nothing spilled.  Of the bounds below (at most 168 VGPRs for
-// stochastic rounding, whose Philox latency needs three waves per SIMD; at most 128
-// for round to nearest) only the float32 round-to-nearest variants reach theirs.
+// and converts each element once, so the bf16 2D variants take 42-61 VGPRs (grouped
+// 69-85) with nothing spilled.  Of the bounds below (at most 168 VGPRs for stochastic
+// rounding, whose Philox latency needs three waves per SIMD; at most 128 for round to
+// nearest) only the float32 round-to-nearest variants reach theirs.
 // Spilled registers cost HBM writes here, not only latency: every wave's spill
 // lines end up evicted by the streaming traffic.
 template <typename T, int VEC, bool SR, int WR, bool GROUPED, int WC, bool ONED, bool PAIR>
 __global__ __launch_bounds__(64 * WR * WC)
-__attribute__((amdgpu_waves_per_eu(VEC && SR ? (ONED && (VEC & 1) ? 2 : 3) : (VEC ? 4 : 1)))) void fp4_quantize_kernel(QuantArgs a, QuantArgs a2, uint32_t first)
+__attribute__((amdgpu_waves_per_eu(VEC && SR ? 3 : (VEC ? 4 : 1)))) void fp4_quantize_kernel(QuantArgs a, QuantArgs a2, uint32_t first)
 {
     static_assert(!(ONED && GROUPED), "grouped tensors use 2D blocks");
     static_assert(WR == 4 || (WR == 1 && !ONED && !GROUPED), "a strip of its own: dense 2D blocks of 32");
