@@ -548,11 +548,23 @@ python3 $R/bench.py --summarize-profiles $O"""
 
 
 
+DETAIL = "bench detail: "
+
+
+def printed(rec: dict) -> tuple:
+    """(result line, detail line) of a run.  The detail line holds everything; the result
+    line names the other workloads by their rates only, since with their kernels it
+    grew to 24 KB, longer than some readers of a program's last line keep."""
+    short = {n: {k: o[k] for k in ("TFLOP/s", "ms_per_step")} for n, o in rec.get("other_workloads", {}).items()}
+    return json.dumps(dict(rec, other_workloads=short) if short else rec), DETAIL + json.dumps(rec)
+
+
 def _json_line(path):
+    """The record of a run's log: its detail line where it has one."""
     with open(path) as f:
-        for line in f:
-            if line.startswith("{"):
-                return json.loads(line)
+        lines = f.read().splitlines()
+    for line in [x[len(DETAIL):] for x in lines if x.startswith(DETAIL)] + [x for x in lines if x.startswith("{")]:
+        return json.loads(line)
     raise ValueError("no JSON line in " + path)
 
 
@@ -823,7 +835,9 @@ def main():
     if not args.no_cpu_baseline:
         rec["cpu_baseline"] = cpu_baseline(synth.WORKLOADS[args.workload](device=dev),
                                            args.cpu_sample_tokens)
-    print(json.dumps(rec), flush=True)
+    line, detail = printed(rec)
+    print(detail, file=sys.stderr, flush=True)
+    print(line, flush=True)
 
 
 if __name__ == "__main__":

@@ -18,6 +18,7 @@ import ctypes
 import json
 import os
 import re
+import shutil
 import subprocess
 import sys
 
@@ -54,6 +55,9 @@ class _Launch(ctypes.Structure):
 
 
 def record(calls, tmp_path):
+    if shutil.which("gcc") is None:
+        import pytest
+        pytest.skip("gcc not found")
     so = os.path.join(str(tmp_path), "launch_recorder.so")
     if not os.path.exists(so):
         subprocess.run(["gcc", "-std=c99", "-O1", "-Wall", "-shared", "-fPIC", "-o", so,

@@ -80,3 +80,23 @@ def test_more_than_one_gpu_is_refused():
     r = subprocess.run([sys.executable, os.path.join(ROOT, "bench.py"), "--gpus", "2"], capture_output=True,
                        text=True, timeout=120)
     assert r.returncode == 2 and "one GPU" in r.stderr
+
+
+def test_result_line_is_short_and_the_detail_complete(tmp_path):
+    import json
+    kinds = {"gemm_fp4": {"achieved": 1.0, "launches_timed": 3}}
+    rec = {"metric": "m", "value": 1.5, "kinds": kinds,
+           "other_workloads": {"w%d" % i: {"TFLOP/s": 2.0, "ms_per_step": 3.0, "kinds": kinds, "launches": 7,
+                                           "per_kernel": {"X" * 40: 1}} for i in range(8)}}
+    line, detail = bench.printed(rec)
+    got = json.loads(line)
+    assert got["value"] == 1.5 and got["kinds"] == kinds
+    assert got["other_workloads"]["w7"] == {"TFLOP/s": 2.0, "ms_per_step": 3.0}
+    # both in one log, in either order: the record read back is the complete one
+    for lines in ((detail, line), (line, detail)):
+        log = tmp_path / "log"
+        log.write_text("\n".join(("bench: measured", *lines)) + "\n")
+        assert bench._json_line(str(log)) == rec
+    log.write_text(line + "\n")
+    assert bench._json_line(str(log)) == got
+    assert json.loads(bench.printed({"value": 1})[0]) == {"value": 1}
